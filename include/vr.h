@@ -237,8 +237,7 @@ vr_status vr_render_noalloc(const vr_volume *vol, const vr_blocks *blocks, const
  * solved along x, then y, then z (fp32 elimination with FP64-derived
  * pivots).  Render the coefficient volume (VR_F32) with vr_render; its
  * vr_build_blocks min/max bound the reconstructed values exactly, so skipping
- * stays exact.  Enqueued on `stream` (the host waits once for a small pivot
- * table).  Errors: VR_E_INVALID_ARG, VR_E_UNSUPPORTED, VR_E_OOM, VR_E_DEVICE. */
+ * stays exact.  Enqueued on `stream`; allocates nothing.  Errors: VR_E_INVALID_ARG, VR_E_UNSUPPORTED, VR_E_OOM, VR_E_DEVICE. */
 vr_status vr_prefilter_bspline(const vr_volume *vol, float *coeff_out, void *stream);
 
 /* Local lighting.  The paper lights its renderings with Phong's model, the

@@ -113,9 +113,8 @@ hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t s);
 // Catmull-Rom samples leave their taps' range by at most this fraction of it.
 constexpr float kCatmullRomWiden = 0.4765625f;  // ((1 + 2/8)^3 - 1) / 2
 hipError_t launch_widen_minmax(const float2 *in, float2 *out, int64_t n, float w, hipStream_t s);
-// coef: per axis (x, y, z) 2 n floats: 1 / pivot[i], then the eliminated
-// super-diagonal sup[i] of the prefilter's tridiagonal system.
-hipError_t launch_prefilter(const VolConst &v, float *out, const float *coef, hipStream_t s);
+// Interpolating B-spline coefficients of `v` into `out` (prefilter.hip).
+hipError_t launch_prefilter(const VolConst &v, float *out, hipStream_t s);
 hipError_t launch_bricked_pass(const BrickedArgs &a, hipStream_t s);
 hipError_t launch_bricked_finish(const float4 *state, float4 *out, int64_t n, hipStream_t s);
 hipError_t launch_preint_table(const float *tf, int K, float step, float4 *out, uint32_t *status, hipStream_t s);

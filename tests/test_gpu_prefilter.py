@@ -1,0 +1,37 @@
+"""Interpolating-spline prefilter at the edges of its segment split: rows of
+one to sixteen voxels per lane (and past them), lines of one to sixteen
+segments of 64 (and past them), every dtype, against the FP64 oracle."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+import paper_2005_01442_amd as vr  # noqa: E402
+from gpu_util import log, upload_volume  # noqa: E402
+
+SHAPES_XYZ = [(1, 1, 1), (2, 3, 1), (1, 64, 65), (63, 65, 2), (64, 16, 17), (65, 129, 33), (513, 5, 3), (1024, 2, 64),
+              (1025, 3, 2), (3, 1024, 2), (2, 1025, 3), (5, 2, 1023), (2, 1, 1100)]
+
+
+@pytest.mark.parametrize("shape", SHAPES_XYZ, ids=str)
+@pytest.mark.parametrize("dtype", [np.int16, np.uint16, np.float32], ids=lambda d: d.__name__)
+def test_prefilter_segments(shape, dtype):
+    nx, ny, nz = shape
+    rng = np.random.default_rng(nx * 7 + ny * 3 + nz)
+    lo, hi = (0, 4096) if dtype == np.uint16 else (-1024, 3072)
+    vol = rng.integers(lo, hi, (nz, ny, nx)).astype(dtype)
+    ref = oracle.prefilter(vol)
+    got = vr.vr_prefilter_bspline(upload_volume(vol)).tensor.cpu().numpy().astype(np.float64)
+    # the inverse of one axis has norm 3, so |c| <= 27 max|v|; each axis rounds
+    # a handful of times per voxel, its errors damped by 0.27 per voxel both
+    # ways: under 8 eps of the largest coefficient per axis
+    bound = 3 * 8 * 2.0**-24 * 27 * np.abs(vol.astype(np.float64)).max()
+    d = np.abs(got - ref).max()
+    log(f"prefilter {shape} {dtype.__name__}: max |d| {d:.3e} of {bound:.3e}")
+    assert d <= bound

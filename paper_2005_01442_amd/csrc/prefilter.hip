@@ -83,6 +83,13 @@ __device__ inline void load_run(const void *src, int64_t i, float v[EM]) {
   }
 }
 
+// Product of two runs' factors, kept from underflowing to 0: the carry of a
+// line that holds an infinity stays an infinity.
+__device__ inline float carry_product(float p, float q) {
+  const float r = p * q;
+  return p == 0.0f || q == 0.0f ? 0.0f : copysignf(fmaxf(fabsf(r), 1.17549435e-38f), r);
+}
+
 // x axis, with the conversion to fp32: one wavefront per row, lane l solves
 // voxels [l EM, l EM + EM), read and written as wide runs, and the carries
 // come from scans of the lanes' affine maps.  (Staging the row through LDS
@@ -93,8 +100,6 @@ template <int DT, int EM>
 __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, float *dst, int nx, int64_t rows,
                                                             const PrefilterCoef coef, float last) {
   constexpr int kHead = kPivots / EM;  // lanes whose pivots are not settled
-  // lanes further back than 64 voxels carry under 1e-36 of their values
-  constexpr int kReach = EM == 1 ? kWaveSize : 2 * kWaveSize / EM;
   __shared__ float pivots[kPivots + EM];
   if (threadIdx.x < kPivots + EM) pivots[threadIdx.x] = coef.u[min((int)threadIdx.x, kPivots - 1)];
   __syncthreads();
@@ -129,11 +134,11 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
     P *= -u[j];
   }
 #pragma unroll
-  for (int off = 1; off < kReach && off < kWaveSize; off <<= 1) {
+  for (int off = 1; off < kWaveSize; off <<= 1) {
     const float a = __shfl_up(P, off, kWaveSize), b = __shfl_up(y, off, kWaveSize);
     if (lane >= off) {
       y = fmaf(P, b, y);
-      P *= a;
+      P = carry_product(P, a);
     }
   }
   y = __shfl_up(y, 1, kWaveSize);
@@ -145,7 +150,10 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
   }
   if (cnt <= EM) {  // the last row takes nothing from beyond
 #pragma unroll
-    for (int j = 0; j < EM; ++j) u[j] = j < cnt - 1 ? u[j] : 0.0f;
+    for (int j = 0; j < EM; ++j) {
+      u[j] = j < cnt - 1 ? u[j] : 0.0f;
+      v[j] = j < cnt ? v[j] : 0.0f;
+    }
   }
   float x = 0.0f, Q = 1.0f;
 #pragma unroll
@@ -154,11 +162,11 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
     Q *= -u[j];
   }
 #pragma unroll
-  for (int off = 1; off < kReach && off < kWaveSize; off <<= 1) {
+  for (int off = 1; off < kWaveSize; off <<= 1) {
     const float a = __shfl_down(Q, off, kWaveSize), b = __shfl_down(x, off, kWaveSize);
     if (lane + off < kWaveSize) {
       x = fmaf(Q, b, x);
-      Q *= a;
+      Q = carry_product(Q, a);
     }
   }
   x = __shfl_down(x, 1, kWaveSize);

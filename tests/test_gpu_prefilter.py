@@ -35,3 +35,16 @@ def test_prefilter_segments(shape, dtype):
     d = np.abs(got - ref).max()
     log(f"prefilter {shape} {dtype.__name__}: max |d| {d:.3e} of {bound:.3e}")
     assert d <= bound
+
+
+@pytest.mark.parametrize("shape", [(65, 3, 3), (700, 2, 2), (3, 300, 2), (2, 3, 200)], ids=str)
+def test_infinite_voxel_reaches_its_lines(shape):
+    """An infinite voxel makes every coefficient infinite, with the sign that
+    alternates along each axis, as sweeps over whole lines give; no NaN."""
+    nx, ny, nz = shape
+    vol = np.ones((nz, ny, nx), np.float32)
+    at = (nz // 2, ny // 2, nx // 3)
+    vol[at] = np.inf
+    got = vr.vr_prefilter_bspline(upload_volume(vol)).tensor.cpu().numpy()
+    z, y, x = np.meshgrid(np.arange(nz) - at[0], np.arange(ny) - at[1], np.arange(nx) - at[2], indexing="ij")
+    assert np.array_equal(got, np.where((z + y + x) % 2 == 0, np.inf, -np.inf).astype(np.float32))

@@ -279,8 +279,7 @@ vr_status vr_build_blocks(const vr_volume *vol, int32_t block_edge, void *stream
   vc.nbz = b->nbz;
   vc.edge = block_edge;
   vc.edge_shift = __builtin_ctz((unsigned)block_edge);
-  e = launch_block_minmax(vc, b->minmax, (hipStream_t)stream);
-  if (e == hipSuccess) e = launch_widen_minmax(b->minmax, b->minmax_cr, (int64_t)nb, kCatmullRomWiden, (hipStream_t)stream);
+  e = launch_block_minmax(vc, b->minmax, b->minmax_cr, kCatmullRomWiden, (hipStream_t)stream);
   if (e != hipSuccess) {
     (void)hipFree(b->minmax);
     delete b;

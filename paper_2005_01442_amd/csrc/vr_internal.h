@@ -95,7 +95,8 @@ int64_t tile_order_count(const RenderArgs &a);
 // of LDS each (0 when it cannot be found out).
 int64_t resident_workgroups(const void *fn, uint32_t lds);
 hipError_t launch_render_backward(const BackwardArgs &a, hipStream_t s);
-hipError_t launch_block_minmax(const VolConst &v, float2 *out, hipStream_t s);
+// Block ranges into `out`, widened by the fraction `widen` of each into `wide`.
+hipError_t launch_block_minmax(const VolConst &v, float2 *out, float2 *wide, float widen, hipStream_t s);
 hipError_t launch_block_occupancy(const VolConst &v, const TfConst &tf, uint8_t *occ, hipStream_t s);
 // The same decisions packed 32 blocks to a word (ceil(nb / 32) words).
 hipError_t launch_occupancy_bits(const VolConst &v, const TfConst &tf, uint32_t *bits, hipStream_t s);
@@ -112,7 +113,6 @@ inline size_t occupancy_bytes(const VolConst &v) {
 hipError_t launch_fill_zero(float *p, int64_t n, hipStream_t s);
 // Catmull-Rom samples leave their taps' range by at most this fraction of it.
 constexpr float kCatmullRomWiden = 0.4765625f;  // ((1 + 2/8)^3 - 1) / 2
-hipError_t launch_widen_minmax(const float2 *in, float2 *out, int64_t n, float w, hipStream_t s);
 // Interpolating B-spline coefficients of `v` into `out` (prefilter.hip).
 hipError_t launch_prefilter(const VolConst &v, float *out, hipStream_t s);
 hipError_t launch_bricked_pass(const BrickedArgs &a, hipStream_t s);

@@ -1229,7 +1229,7 @@ __device__ inline void walk(const VolConst &v, const TfShared &s, const TfConst 
 }
 
 // ---------------------------------------------------------------------------
-// Ray groups.  G consecutive lanes (within a quad) march one ray: at each step
+// Ray groups.  G consecutive lanes (1, 2, 4 or 16) march one ray: at each step
 // of the wavefront, lane j of a group takes lattice index k + j and the
 // wavefront advances G indices.  A wavefront then holds 64 / G rays and
 // finishes them in about 1 / G of the steps, so the longest tiles of an image
@@ -1246,16 +1246,26 @@ __device__ inline void walk(const VolConst &v, const TfShared &s, const TfConst 
 // ---------------------------------------------------------------------------
 
 // Lane I of each ray group, to every lane of the group (a DPP quad
-// permutation: [I, I, 2 + I, 2 + I] for pairs, [I, I, I, I] for quads).
+// permutation: [I, I, 2 + I, 2 + I] for pairs, [I, I, I, I] for quads; a row
+// broadcast for groups of 16).
 template <int G, int I>
 __device__ inline float from_group_lane(float x) {
   if constexpr (G == 1) {
     return x;
+  } else if constexpr (G == 16) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + I, 0xF, 0xF, true));
   } else {
     constexpr int hi = G == 2 ? 2 + I : I;
     constexpr int ctrl = I | (I << 2) | (hi << 4) | (hi << 6);
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), ctrl, 0xF, 0xF, false));
   }
+}
+
+// f(integral_constant<int, 0>), .., f(integral_constant<int, N - 1>).
+template <int N, int I = 0, class F>
+__device__ inline void for_each_index(F &f) {
+  f(std::integral_constant<int, I>{});
+  if constexpr (I + 1 < N) for_each_index<N, I + 1>(f);
 }
 
 // A classified sample as it enters the compositing chain: colour and
@@ -1414,12 +1424,7 @@ __device__ inline int walk_group(const VolConst &v, const TfShared &s, const TfC
       if (at) own = ChainState{ta, C0, C1, C2, T};
       if (ert_on && (1.0f - T) >= mc.ert) live = false;
     };
-    link(std::integral_constant<int, 0>{});
-    if constexpr (G > 1) link(std::integral_constant<int, 1>{});
-    if constexpr (G > 2) {
-      link(std::integral_constant<int, 2>{});
-      link(std::integral_constant<int, 3>{});
-    }
+    for_each_index<G>(link);
     alive = live;
     take(mine, own);
     if constexpr (FLAT)

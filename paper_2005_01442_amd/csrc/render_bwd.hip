@@ -610,20 +610,6 @@ static hipError_t launch_bwd_as(const BackwardArgs &a0, uint32_t lds, hipStream_
   return hipGetLastError();
 }
 
-// Largest distance, in voxels, between neighbouring rays of the launch's views
-// at the volume's centre.
-static double ray_pitch(const RenderArgs &a) {
-  const double p[3] = {0.5 * (a.vol.nx - 1), 0.5 * (a.vol.ny - 1), 0.5 * (a.vol.nz - 1)};
-  double most = 0.0;
-  for (int v = 0; v < a.n_views; ++v) {
-    const CamConst &c = a.cams[v];
-    double z = 0.0;
-    for (int k = 0; k < 3; ++k) z += (p[k] - c.eye[k]) * c.fwd[k];
-    most = std::max(most, c.proj != 0 ? 2.0 * std::max(z, 0.0) * c.th / c.H : 2.0 * std::max(c.hw / c.W, c.hh / c.H));
-  }
-  return most;
-}
-
 hipError_t launch_render_backward(const BackwardArgs &a0, hipStream_t s) {
   BackwardArgs a = a0;
   const RenderArgs &ra = a.r;

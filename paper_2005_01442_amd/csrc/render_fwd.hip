@@ -1,148 +1,13 @@
-// render_fwd.hip -- forward ray casting kernel (gfx950).
-//
-// Per pixel (Section 2 of the paper): cast a ray from the camera, clip it to
-// the volume box, march the midpoint lattice with the fixed step, reconstruct
-// the scalar with the tricubic B-spline, classify through the TF
-// (post-classification), composite front to back, stop once the opacity
-// reaches the threshold, and leap over blocks that cannot be visible.
-#include <algorithm>
-
-#include "vr_internal.h"
+// render_fwd.hip -- forward ray casting (gfx950): the unlit whole-image kernel,
+// the workgroup order, launch rules, and the serving kernel.
+#include "render_march.h"
 
 namespace vr {
 
-// One sample's classified colour and extinction at (px, py, pz): the value (or,
-// lit, value and gradient) reconstructed from the LDS box when the step's
-// stencils lie in it, else from global memory, then classified through the TF
-// (post-classification; pre-classification for F == 2).  SHADE lights the
-// classified colour with the gradient of the same 64 taps (the value, hence
-// opacity and termination, is unchanged).
-template <int DT, bool SHADE, int F>
-__device__ inline Classified eval_sample(const VolConst &v, const TfShared &s, const TfConst &tf, float tf_v0,
-                                         float tf_scale, const ShadeConst &sc, const RayLight &rl,
-                                         __amdgpu_buffer_rsrc_t rs, const ValBox &box, float px, float py, float pz,
-                                         uint32_t &unstaged) {
-  Classified q;
-  if constexpr (SHADE) {
-    StencilG sg = make_stencil_grad(px, py, pz);
-    float4 vg;
-    if (box.valid) {
-      float t[4][4][4];
-      load_taps_box(box, sg.s, t);
-      vg = combine_grad(sg, t);
-    } else {
-      vg = reconstruct_grad<DT>(rs, v, sg);
-      ++unstaged;
-    }
-    q = classify(s, tf.K, tf.v0, tf.scale, vg.x);
-    light_colour(sc, rl, vg, q.c);
-  } else if constexpr (F == 2) {
-    Stencil st = make_stencil(px, py, pz);
-    float t[4][4][4];
-    if (box.valid) {
-      load_taps_box(box, st, t);
-    } else {
-      load_taps<DT>(rs, v, st, t);
-      ++unstaged;
-    }
-    q = preclassify(s, tf.K, tf.v0, tf.scale, st, t);
-  } else {
-    Stencil st = make_stencil_f<F>(px, py, pz);
-    float val;
-    if (box.valid) {
-      val = reconstruct_box(box, st);
-    } else {
-      val = reconstruct<DT>(rs, v, st);
-      ++unstaged;
-    }
-    q = classify(s, tf.K, tf_v0, tf_scale, val);
-  }
-  return q;
-}
-
-// March one ray front to back, one ray per lane.  Skipped samples are exactly
-// those whose block is empty under the TF; such a sample would contribute
-// a = 0 exactly, so the result is bit-identical to marching every sample.
-template <int DT, bool SHADE, int F = 0>
-__device__ inline float4 march(const VolConst &v, const TfShared &s, const TfConst &tf, const MarchConst &mc,
-                               const ShadeConst &sc, const Ray &r, __amdgpu_buffer_rsrc_t rs, ValBox &box,
-                               uint32_t &evaluated, uint32_t &unstaged) {
-  float C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, T = 1.0f;
-  const float sl2 = mc.step * 1.4426950408889634f;
-  float tf_v0 = tf.v0, tf_scale = tf.scale;  // held in registers (as the walk's grid constants)
-  asm volatile("" : "+v"(tf_v0), "+v"(tf_scale));
-  const bool ert_on = mc.ert > 0.0f && mc.ert < 1.0f;
-  RayLight rl;
-  if constexpr (SHADE) rl = ray_light(sc, r.d);
-  // lighting and pre-classification hold more registers: two box rows in
-  // flight per lane
-  constexpr int kFillBatch = SHADE || F == 2 ? 2 : 4;
-  auto prep = [&](bool want, float px, float py, float pz) {
-    if (box.cells) vbox_prepare<DT, kFillBatch>(box, rs, v, r, want, px, py, pz);
-  };
-  auto visit = [&](int, float px, float py, float pz) -> bool {
-    const Classified q = eval_sample<DT, SHADE, F>(v, s, tf, tf_v0, tf_scale, sc, rl, rs, box, px, py, pz, unstaged);
-    float e = transmit(q.c.w, sl2);
-    float ta = T * (1.0f - e);
-    C0 = fmaf(ta, q.c.x, C0);
-    C1 = fmaf(ta, q.c.y, C1);
-    C2 = fmaf(ta, q.c.z, C2);
-    T = T * e;
-    ++evaluated;
-    return !(ert_on && (1.0f - T) >= mc.ert);
-  };
-  NoPost post;
-  walk(v, s, tf, mc, r, visit, prep, post);
-  return make_float4(C0, C1, C2, 1.0f - T);
-}
-
-// The whole-image kernel marches each ray with a group of kRayGroup lanes
-// (see walk_group): pairs, measured against one and four lanes per ray.
-#ifndef VR_RAY_GROUP
-#define VR_RAY_GROUP 2
-#endif
-constexpr int kRayGroup = VR_RAY_GROUP;
-static_assert(kRayGroup == 1 || kRayGroup == 2 || kRayGroup == 4, "ray groups lie within a quad");
-
-template <int G, int DT, bool SHADE, int F, int ZD = VR_VBOX_Z>
-__device__ inline float4 march_group(const VolConst &v, const TfShared &s, const TfConst &tf, const MarchConst &mc,
-                                     const ShadeConst &sc, const Ray &r, __amdgpu_buffer_rsrc_t rs, ValBox &box,
-                                     uint32_t &evaluated, uint32_t &unstaged) {
-  const float sl2 = mc.step * 1.4426950408889634f;
-  float tf_v0 = tf.v0, tf_scale = tf.scale;
-  asm volatile("" : "+v"(tf_v0), "+v"(tf_scale));
-  RayLight rl;
-  if constexpr (SHADE) rl = ray_light(sc, r.d);
-  constexpr int kFillBatch = SHADE || F == 2 ? 2 : 4;
-  auto prep = [&](bool want, float px, float py, float pz) {
-    if (box.cells) vbox_prepare<DT, kFillBatch, ZD>(box, rs, v, r, want, px, py, pz);
-  };
-  auto eval = [&](int, float px, float py, float pz) -> ChainSample {
-    const Classified q = eval_sample<DT, SHADE, F>(v, s, tf, tf_v0, tf_scale, sc, rl, rs, box, px, py, pz, unstaged);
-    return ChainSample{q.c.x, q.c.y, q.c.z, transmit(q.c.w, sl2)};
-  };
-  auto take = [&](bool mine, const ChainState &) { evaluated += mine ? 1u : 0u; };
-  NoFlat flat;
-  NoPost post;
-  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
-  walk_group<G>(v, s, tf, mc, r, eval, prep, take, flat, post, acc);
-  return make_float4(acc.x, acc.y, acc.z, 1.0f - acc.w);
-}
-
-// The LDS value boxes bound the workgroups per CU (14^3 boxes: three, i.e.
-// three wavefronts per SIMD); the register budget is set to match.
-#ifndef VR_FWD_MAX_WAVES
-#define VR_FWD_MAX_WAVES 3
-#endif
-// Unlit 16-bit volumes: registers budgeted for three wavefronts per SIMD (C1:
-// leaving the compiler free measured 1 % slower); fp32 volumes keep the free
-// budget (the C3 forward measured 2 % slower with the limit).
-#ifndef VR_FWD_MIN_WAVES
-#define VR_FWD_MIN_WAVES 3
-#endif
 constexpr uint32_t kLdsPerCu = 160u * 1024u;  // gfx950
 constexpr uint64_t kMallBytes = 256ull << 20;   // MI355X: 256 MB of Infinity Cache (MALL)
 constexpr uint32_t kFwdWgPerCu = VR_FWD_MAX_WAVES;  // four wavefronts per workgroup, one per SIMD
+constexpr int kRayGroup = 2;  // lanes per ray of the serving kernel
 
 // The occupancy bits join the LDS state (after the boxes) when three
 // workgroups still fit on a compute unit; else the kernels read them from
@@ -152,103 +17,6 @@ int32_t occupancy_lds_words(const RenderArgs &a, uint32_t lds) {
   const int64_t words = ((int64_t)a.vol.nbx * a.vol.nby * a.vol.nbz + 31) / 32;
   return (int64_t)lds + words * 4 <= (int64_t)(kLdsPerCu / kFwdWgPerCu) ? (int32_t)words : 0;
 }
-#ifdef VR_TIMELINE
-__device__ unsigned long long g_timeline_fwd[kTimelineWaves * 4];
-static int64_t g_timeline_fwd_records = 0;
-#endif
-
-// One wavefront item: wavefront w of workgroup item i (a part of a
-// super-tile); the counts of its samples are added to the caller's.
-template <int DT, bool SHADE, int F, int ZD>
-__device__ inline void render_wave_item(const RenderArgs &a, const TfShared &s, bool tf_ok, ValBox &box,
-                                        __amdgpu_buffer_rsrc_t rs, int64_t i, int w, uint32_t &evaluated,
-                                        uint32_t &unstaged, uint32_t &lattice, uint32_t &hits) {
-#ifdef VR_TIMELINE
-  const unsigned long long tl0 = __builtin_amdgcn_s_memrealtime();
-#endif
-  int part;
-  const SuperTile st = group_tile_of<kRayGroup>(a.order, i, a.W, a.H, a.n_views, a.chunk_edge, part);
-  if (!st.valid) return;  // uniform over the wavefront
-  int col, row;
-  group_pixel_of<kRayGroup>(st.sx, st.sy, part, w * kWaveSize + (int)(threadIdx.x % kWaveSize), col, row);
-  const bool inside = col < a.W && row < a.H;
-  const bool lead = (threadIdx.x % kRayGroup) == 0;  // the lane that stores its group's pixel
-  if (!tf_ok) {  // uniform: an invalid TF gives NaN pixels
-    if (inside && lead) reinterpret_cast<float4 *>(a.out)[((size_t)st.view * a.H + row) * a.W + col] = nan_rgba();
-    return;
-  }
-  const CamConst &cam = a.cams[st.view];
-  // every lane enters the march (it steps the wavefront in unison); pixels
-  // outside the image carry an empty ray
-  Ray r;
-  r.hit = false;
-  r.ns = 0;
-  r.k0 = 0;
-  if (inside) r = setup_ray(cam, col, row, a.vol.nx, a.vol.ny, a.vol.nz, a.mc.step);
-#ifdef VR_TIMELINE
-  const uint32_t before = evaluated;
-#endif
-  float4 rgba;
-  if constexpr (kRayGroup == 1)
-    rgba = march<DT, SHADE, F>(a.vol, s, a.tf, a.mc, a.shade, r, rs, box, evaluated, unstaged);
-  else
-    rgba = march_group<kRayGroup, DT, SHADE, F, ZD>(a.vol, s, a.tf, a.mc, a.shade, r, rs, box, evaluated, unstaged);
-  if (inside && lead) {
-    float4 *o = reinterpret_cast<float4 *>(a.out);
-    o[((size_t)st.view * a.H + row) * a.W + col] = rgba;
-  }
-  lattice += lead ? (uint32_t)r.ns : 0u;
-  hits += lead && r.hit ? 1u : 0u;
-#ifdef VR_TIMELINE
-  const int tx = (a.W + kSuperEdge - 1) / kSuperEdge, ty = (a.H + kSuperEdge - 1) / kSuperEdge;
-  timeline_record(g_timeline_fwd, (size_t)i * kWavesPerWg + w, tl0, st.view * tx * ty + st.sy * tx + st.sx,
-                  evaluated - before);
-#endif
-}
-
-// ZD: depth of the LDS value boxes (see ValBox).
-template <int DT, bool SHADE, int F, int ZD = VR_VBOX_Z>
-__global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(SHADE ? VR_FWD_MAX_WAVES : (DT == kF32 ? 1 : VR_FWD_MIN_WAVES), VR_FWD_MAX_WAVES)))
-void k_render(const RenderArgs args) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  const RenderArgs &a = kernarg<RenderArgs>();
-  if (!a.queue) {  // one workgroup item per workgroup
-    int part;
-    if (!group_tile_of<kRayGroup>(a.order, blockIdx.x, a.W, a.H, a.n_views, a.chunk_edge, part).valid)
-      return;  // uniform over the workgroup
-  }
-  TfShared s = carve_tf(lds, a.tf.K);
-  if (a.occ_lds_words > 0)
-    stage_occupancy(s, a.vol, lds + vbox_lds_offset(a.tf.K) + vbox_lds_bytes(), a.occ_lds_words);
-  const bool tf_ok = load_tf(s, a.tf);
-  __amdgpu_buffer_rsrc_t rs = make_rsrc(a.vol.data, a.vol.bytes);
-  // the wavefront's LDS value box (its contents stay valid from one item to
-  // the next: the volume is the launch's)
-  ValBox box;
-  box.valid = false;
-  box.ox = box.oy = box.oz = 0;
-  box.cells = a.use_box ? reinterpret_cast<float *>(lds + vbox_lds_offset(a.tf.K)) +
-                              (threadIdx.x / kWaveSize) * kVBoxCells
-                        : nullptr;
-  uint32_t evaluated = 0, unstaged = 0, lattice = 0, hits = 0;
-  if (!a.queue) {
-    render_wave_item<DT, SHADE, F, ZD>(a, s, tf_ok, box, rs, blockIdx.x, (int)(threadIdx.x / kWaveSize), evaluated,
-                                   unstaged, lattice, hits);
-  } else {
-    const int x = (int)(blockIdx.x % kXcds);
-    int w = 0;
-    int64_t i = 0;
-    while (next_wave_item(a.queue, (uint32_t)a.queue_items, x, i, w))
-      render_wave_item<DT, SHADE, F, ZD>(a, s, tf_ok, box, rs, i, w, evaluated, unstaged, lattice, hits);
-  }
-  if (a.counters) {
-    wave_count(a.counters + 0, evaluated);
-    wave_count(a.counters + 1, lattice);
-    wave_count(a.counters + 2, hits);
-    wave_count(a.counters + 3, unstaged);
-  }
-}
-
 // Workgroups of `fn` the current device holds at once with `lds` bytes of
 // LDS each (0 when it cannot be found out).
 int64_t resident_workgroups(const void *fn, uint32_t lds) {
@@ -259,34 +27,6 @@ int64_t resident_workgroups(const void *fn, uint32_t lds) {
     return 0;
   }
   return (int64_t)cus * per;
-}
-
-template <bool SHADE, int F, int ZD = VR_VBOX_Z>
-static hipError_t launch_render_as(const RenderArgs &a0, int64_t grid, uint32_t lds, hipStream_t s) {
-  RenderArgs a = a0;
-  const void *fn = a.vol.dtype == kU16   ? reinterpret_cast<const void *>(&k_render<kU16, SHADE, F, ZD>)
-                   : a.vol.dtype == kI16 ? reinterpret_cast<const void *>(&k_render<kI16, SHADE, F, ZD>)
-                                         : reinterpret_cast<const void *>(&k_render<kF32, SHADE, F, ZD>);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  // with an order (and its queue counters) the launch is queued: as many
-  // workgroups as the device holds, fed wavefront items
-  a.queue = nullptr;
-  a.queue_items = 0;
-  if (a.order) {
-    const int64_t resident = resident_workgroups(fn, lds);
-    if (resident >= kXcds && resident < grid) {
-      a.queue = reinterpret_cast<uint32_t *>(const_cast<int32_t *>(a.order) + tile_order_count(a));
-      a.queue_items = (int32_t)(grid / kXcds * kWavesPerWg);
-      grid = resident;
-    }
-  }
-  switch (a.vol.dtype) {
-  case kU16: hipLaunchKernelGGL((k_render<kU16, SHADE, F, ZD>), dim3((unsigned)grid), dim3(kWgSize), lds, s, a); break;
-  case kI16: hipLaunchKernelGGL((k_render<kI16, SHADE, F, ZD>), dim3((unsigned)grid), dim3(kWgSize), lds, s, a); break;
-  default: hipLaunchKernelGGL((k_render<kF32, SHADE, F, ZD>), dim3((unsigned)grid), dim3(kWgSize), lds, s, a); break;
-  }
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -412,27 +152,50 @@ int32_t *make_tile_order(const RenderArgs &a, hipStream_t s) {
   return order;
 }
 
+double ray_pitch(const RenderArgs &a) {
+  const double p[3] = {0.5 * (a.vol.nx - 1), 0.5 * (a.vol.ny - 1), 0.5 * (a.vol.nz - 1)};
+  double most = 0.0;
+  for (int v = 0; v < a.n_views; ++v) {
+    const CamConst &c = a.cams[v];
+    double z = 0.0;
+    for (int k = 0; k < 3; ++k) z += (p[k] - c.eye[k]) * c.fwd[k];
+    most = std::max(most, c.proj != 0 ? 2.0 * std::max(z, 0.0) * c.th / c.H : 2.0 * std::max(c.hw / c.W, c.hh / c.H));
+  }
+  return most;
+}
+
+// Lanes per ray of a launch.  More lanes per ray make a wavefront's rays fewer
+// and closer: its samples fit the LDS box at larger distances p between rays
+// (8x4 rays of two samples up to p about 1.3, 4x4 of four up to 2.5, 2x2 of
+// sixteen up to 5; a wavefront that does not fit gathers 16 rows per sample from
+// global memory), and a launch of few rays is cut into more and shorter pieces,
+// against a longer compositing chain per sample.  Measured (int16, step 0.5,
+// blocks and ERT; 2 / 4 / 16 lanes): 512^3 to 1024^2, p = 0.97: 1.28 / 1.33 /
+// 2.85 ms; to 700^2, p = 1.4: 1.32 / 0.80 / 1.42; to 400^2, p = 2.5: 1.88 / 0.73 /
+// 0.60; 240^3 to 256^2, p = 1.8: 0.84 / 0.28 / 0.22 ms; to 512^2, p = 0.9: 0.40 /
+// 0.33 / 0.56; 97^3 to 128^2, p = 1.5: 0.31 / 0.15 / 0.11 ms.
+static int ray_group(const RenderArgs &a) {
+  const double p = ray_pitch(a);
+  const int64_t rays = (int64_t)a.n_views * a.W * a.H;
+  if (p > 2.3 || rays <= 20000 || (p > 1.6 && rays <= 80000)) return 16;
+  return p > 1.08 || rays <= 400000 ? 4 : 2;
+}
+
 hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   RenderArgs a = a0;
-  const int64_t grid = group_grid(render_grid(a), kRayGroup);
+  if (a.vol.dtype != kU16 && a.vol.dtype != kI16 && a.vol.dtype != kF32) return hipErrorInvalidValue;
   uint32_t lds = tf_lds_bytes(a.tf.K);
   const uint32_t with_box = vbox_lds_offset(a.tf.K) + vbox_lds_bytes();
   a.use_box = with_box <= max_lds_per_workgroup() ? 1 : 0;
   if (a.use_box) lds = with_box;
   a.occ_lds_words = occupancy_lds_words(a, lds);
   lds += (uint32_t)a.occ_lds_words * 4u;
-  if (a.vol.dtype != kU16 && a.vol.dtype != kI16 && a.vol.dtype != kF32) return hipErrorInvalidValue;
-#ifdef VR_TIMELINE
-  g_timeline_fwd_records = grid * (kWgSize / kWaveSize);
-#endif
-  if (a.shaded) return launch_render_as<true, 0>(a, grid, lds, s);
-  if (a.filter == 1) return launch_render_as<false, 1>(a, grid, lds, s);
-  if (a.filter == 2) return launch_render_as<false, 2>(a, grid, lds, s);
-  if (a.filter == 3) return launch_render_as<false, 3>(a, grid, lds, s);
+  const int group = ray_group(a);
+  if (a.shaded || a.filter != 0) return launch_render_variant(a, group, lds, s);
   // the shallow value box for volumes the MALL holds (their refills are
   // cheap, its fill passes fewer), the deep one above
-  if (a.use_box && a.vol.bytes <= kMallBytes) return launch_render_as<false, 0, kVBoxShallow>(a, grid, lds, s);
-  return launch_render_as<false, 0>(a, grid, lds, s);
+  if (group == 2 && a.use_box && a.vol.bytes <= kMallBytes) return launch_render_as<2, false, 0, kVBoxShallow>(a, lds, s);
+  return launch_render_grouped<false, 0>(a, group, lds, s);
 }
 
 // Serving: kRayGroup workgroups per work item, a 16x16 super-tile of one

@@ -1160,9 +1160,9 @@ __device__ inline void lattice_point(const Ray &r, float step, int k, float &px,
 __device__ inline bool block_occupied(const VolConst &v, const TfShared &s, const TfConst &tf, int b);
 __device__ inline int empty_radius(const VolConst &v, int b);
 
-// Walk one ray's lattice with the whole wavefront in step: all lanes look at
-// the same index k (a thin slab of the tile's rays).  A lane sits out when k
-// is outside its ray, after its ray terminated, or when its sample lies in a
+// Walk a tile's rays with the whole wavefront in step: all lanes look at
+// the same indices (a thin slab of the tile's rays).  A lane sits out when its
+// index is outside its ray, after its ray terminated, or when its sample lies in a
 // block that is empty under the TF (such a sample would add exactly zero).
 // When no lane has a sample to evaluate, the wavefront leaps to the smallest
 // index any lane may need: its next lattice start, or the first index that
@@ -1170,7 +1170,6 @@ __device__ inline int empty_radius(const VolConst &v, int b);
 // the launch carries the radius plane (the lane sits out until then, without
 // looking at its samples).  prep(want, px, py, pz) runs on every lane of the
 // wavefront before the samples of a step (for wavefront-wide staging);
-// visit(k, px, py, pz) evaluates one sample and returns false to stop the ray.
 // post() runs on every lane after the samples of a step.
 struct NoPrep {
   __device__ inline void operator()(bool, float, float, float) const {}
@@ -1178,55 +1177,6 @@ struct NoPrep {
 struct NoPost {
   __device__ inline void operator()() const {}
 };
-
-// FROM: start at lattice index kstart (>= r.k0) instead of r.k0 -- a ray
-// resumed where an earlier pass left it; positions still follow r.
-template <class Visit, class Prep, class Post, bool FROM = false>
-__device__ inline void walk(const VolConst &v, const TfShared &s, const TfConst &tf, const MarchConst &mc,
-                            const Ray &r, Visit &visit, Prep &prep, Post &post, int kstart = 0) {
-  const int kb = r.hit ? (FROM ? max(r.k0, kstart) : r.k0) : 0x7fffffff;
-  const int ke = r.hit ? r.k0 + r.ns : 0;
-  bool alive = r.hit;
-  int k = wave_min_i32(kb);
-  const int kend = wave_max_i32(ke);
-  int kfree = kb;  // indices below kfree: before the ray, or left in an empty block
-  // the grid constants of the per-step block lookup and leap held in
-  // registers, so the loop does not re-read them from the kernel arguments
-  // (a scalar load whose wait also drains the wavefront's LDS reads)
-  VolConst vg = v;
-  asm volatile("" : "+v"(vg.nx), "+v"(vg.ny), "+v"(vg.nz), "+v"(vg.edge_shift), "+v"(vg.nbx), "+v"(vg.nby));
-  int cur_block = -1;
-  bool cur_occ = false;
-  int bc[3] = {0, 0, 0};
-  while (k < kend) {
-    const bool in = alive && k >= kfree && k < ke;
-    bool want = in;
-    // every lane computes its position and cell (used by in-lanes only), so the
-    // floors dominate, and are shared with, the box test and the stencil
-    float px, py, pz;
-    lattice_point(r, mc.step, k, px, py, pz);
-    const int ix = (int)floorf(px), iy = (int)floorf(py), iz = (int)floorf(pz);
-    if (in && mc.skip) {
-      const int b = block_of_cell(vg, ix, iy, iz, bc);
-      if (b != cur_block) {
-        cur_block = b;
-        cur_occ = block_occupied(v, s, tf, b);
-      }
-      want = cur_occ;
-    }
-    if (__ballot(want) == 0ull) {
-      if (in) kfree = leap_target(vg, r, bc, mc.step, k, empty_radius(v, cur_block));
-      const int prop = alive && k < ke ? kfree : 0x7fffffff;
-      const int m = wave_min_i32(prop);
-      k = m > k + 1 ? m : k + 1;
-      continue;
-    }
-    prep(want, px, py, pz);
-    if (want && !visit(k, px, py, pz)) alive = false;
-    post();
-    ++k;
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Ray groups.  G consecutive lanes (1, 2, 4 or 16) march one ray: at each step
@@ -1236,7 +1186,7 @@ __device__ inline void walk(const VolConst &v, const TfShared &s, const TfConst 
 // -- the rays through the whole volume, which set a kernel's length -- are
 // split into G times as many, G times shorter pieces of work.
 //
-// Each lane evaluates its own sample (skipping, leaps and staging as in walk);
+// Each lane evaluates its own sample (with the skipping, leaps and staging above);
 // the group's G samples are then composited front to back in index order by
 // every lane of the group, with the one-lane march's operations in its order,
 // so colour, transmittance and the termination sample are bit-identical to
@@ -1280,11 +1230,10 @@ struct ChainState {
   float ta, C0, C1, C2, T;
 };
 
-// walk for ray groups.  eval(k, px, py, pz) -> ChainSample evaluates this
-// lane's sample (called only where the ray takes it); take(mine, own) runs on
-// every lane after the chain, `mine` telling whether this lane's sample was
-// composited and `own` the ray's state right after it; prep and post as in
-// walk.  acc carries the ray's (C0, C1, C2, T) in and out.
+// The walk.  eval(k, px, py, pz) -> ChainSample evaluates this lane's sample
+// (called only where the ray takes it); take(mine, own) runs on every lane
+// after the chain, `mine` telling whether this lane's sample was composited and
+// `own` the ray's state right after it; prep and post as above.  acc carries the ray's (C0, C1, C2, T) in and out.
 //
 // FLAT (kernels that visit every sample, mc.flat set): a sample in a block
 // that is empty under the TF and constant over its footprint is not
@@ -1557,12 +1506,18 @@ __device__ inline SuperTile group_tile_of(const int32_t *order, int64_t wg, int 
 }
 
 // Pixel of the ray of thread t of a workgroup item: wavefront w = t / 64 of
-// part p covers a TW x TH block (8x8, 8x4, 4x4 for G = 1, 2, 4), ray
-// r = (t mod 64) / G the pixel (r mod TW, r / TW) of it.
+// part p covers a TW x TH block (8x8, 8x4, 4x4, 2x2 for G = 1, 2, 4, 16), ray
+// r = (t mod 64) / G the pixel (r mod TW, r / TW) of it; a part is 16 / G rows
+// of the super-tile, or with G = 16 a 4x4 block of it.
 template <int G>
 __device__ inline void group_pixel_of(int sx, int sy, int part, int t, int &col, int &row) {
-  constexpr int TW = G <= 2 ? 8 : 4, TH = kWaveSize / G / TW, WX = kSuperEdge / TW;
   const int wave = t / kWaveSize, ray = (t % kWaveSize) / G;
+  if constexpr (G == 16) {
+    col = sx * kSuperEdge + (part % 4) * 4 + (wave % 2) * 2 + ray % 2;
+    row = sy * kSuperEdge + (part / 4) * 4 + (wave / 2) * 2 + ray / 2;
+    return;
+  }
+  constexpr int TW = G <= 2 ? 8 : 4, TH = kWaveSize / G / TW, WX = kSuperEdge / TW;
   col = sx * kSuperEdge + (wave % WX) * TW + ray % TW;
   row = sy * kSuperEdge + part * (kSuperEdge / G) + (wave / WX) * TH + ray / TW;
 }

@@ -72,6 +72,12 @@ uint32_t max_lds_per_workgroup();
 int32_t chunk_edge_setting();
 
 hipError_t launch_render(const RenderArgs &a, hipStream_t s);
+// The same with local lighting or another filter (a.shaded, a.filter; `group`
+// lanes per ray and `lds` bytes as launch_render has chosen).
+hipError_t launch_render_variant(const RenderArgs &a, int group, uint32_t lds, hipStream_t s);
+// Largest distance, in voxels, between neighbouring rays of the launch's views
+// at the volume's centre.
+double ray_pitch(const RenderArgs &a);
 // Words of a.vol.occ a render launch stages in LDS after `lds` bytes of
 // other state (0: read from global memory).
 int32_t occupancy_lds_words(const RenderArgs &a, uint32_t lds);

@@ -1,0 +1,51 @@
+"""The lanes marching a ray (16, 4 or 2, by the number of rays and the distance
+between them) change nothing: a view rendered alone equals the same view
+rendered among others bit for bit, and coarse views match the oracle."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+import paper_2005_01442_amd as vr  # noqa: E402
+from gpu_util import compare_with_flags, gpu_render, upload_tf, upload_volume  # noqa: E402
+
+DIMS = (49, 45, 42)
+
+
+def _volume(dtype):
+    vol = synth.ct_phantom_i16(*DIMS, seed=140, n_soft=5, n_bone=4)
+    return vol if dtype == np.int16 else vol.astype(np.float32)
+
+
+@pytest.mark.parametrize("size", [(160, 120), (180, 160)], ids=["16_and_4_lanes", "4_and_2_lanes"])
+@pytest.mark.parametrize("how", ["unlit", "lit", "catmull_rom", "preclassified", "trilinear"])
+def test_one_view_equals_the_same_among_sixteen(size, how):
+    filt = {"catmull_rom": vr.VR_FILTER_CATMULL_ROM, "preclassified": vr.VR_FILTER_BSPLINE_PRECLASSIFIED,
+            "trilinear": vr.VR_FILTER_TRILINEAR}.get(how, 0)
+    light = vr.Shading(**synth.SHADE_CT) if how == "lit" else None
+    cams = synth.orbit_cameras(DIMS, 16, 141, 60.0, *size)
+    tf = upload_tf(synth.tf1())
+    for dtype in (np.int16, np.float32):
+        vol = upload_volume(_volume(dtype))
+        blocks = vr.vr_build_blocks(vol, 8)
+        for step, ert, skip in ((0.5, 0.99, True), (1.3, 0.0, False)):
+            many = vr.vr_render(vol, blocks, cams, tf, step, ert, skip, shading=light, filter=filt)
+            one = vr.vr_render(vol, blocks, cams[3:4], tf, step, ert, skip, shading=light, filter=filt)
+            assert torch.equal(one[0], many[3]), (dtype, step)
+
+
+@pytest.mark.parametrize("size", [7, 16, 31, 44])
+def test_coarse_views_match_oracle(size):
+    """Rays 2 to 14 voxels apart, ragged tiles, odd rows."""
+    vol = _volume(np.int16)
+    cams = synth.orbit_cameras(DIMS, 3, 142, 60.0, size + 2, size)
+    ref = oracle.render(vol, cams, synth.tf1(), 0.5, ert=0.99)
+    got = gpu_render(vol, cams, synth.tf1(), 0.5, 0.99, True, block_edge=8)
+    compare_with_flags(got, ref["rgba"], ref["flags"], 0.99)

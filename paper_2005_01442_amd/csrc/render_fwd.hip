@@ -7,7 +7,6 @@ namespace vr {
 constexpr uint32_t kLdsPerCu = 160u * 1024u;  // gfx950
 constexpr uint64_t kMallBytes = 256ull << 20;   // MI355X: 256 MB of Infinity Cache (MALL)
 constexpr uint32_t kFwdWgPerCu = VR_FWD_MAX_WAVES;  // four wavefronts per workgroup, one per SIMD
-constexpr int kRayGroup = 2;  // lanes per ray of the serving kernel
 
 // The occupancy bits join the LDS state (after the boxes) when three
 // workgroups still fit on a compute unit; else the kernels read them from
@@ -152,35 +151,6 @@ int32_t *make_tile_order(const RenderArgs &a, hipStream_t s) {
   return order;
 }
 
-double ray_pitch(const RenderArgs &a) {
-  const double p[3] = {0.5 * (a.vol.nx - 1), 0.5 * (a.vol.ny - 1), 0.5 * (a.vol.nz - 1)};
-  double most = 0.0;
-  for (int v = 0; v < a.n_views; ++v) {
-    const CamConst &c = a.cams[v];
-    double z = 0.0;
-    for (int k = 0; k < 3; ++k) z += (p[k] - c.eye[k]) * c.fwd[k];
-    most = std::max(most, c.proj != 0 ? 2.0 * std::max(z, 0.0) * c.th / c.H : 2.0 * std::max(c.hw / c.W, c.hh / c.H));
-  }
-  return most;
-}
-
-// Lanes per ray of a launch.  More lanes per ray make a wavefront's rays fewer
-// and closer: its samples fit the LDS box at larger distances p between rays
-// (8x4 rays of two samples up to p about 1.3, 4x4 of four up to 2.5, 2x2 of
-// sixteen up to 5; a wavefront that does not fit gathers 16 rows per sample from
-// global memory), and a launch of few rays is cut into more and shorter pieces,
-// against a longer compositing chain per sample.  Measured (int16, step 0.5,
-// blocks and ERT; 2 / 4 / 16 lanes): 512^3 to 1024^2, p = 0.97: 1.28 / 1.33 /
-// 2.85 ms; to 700^2, p = 1.4: 1.32 / 0.80 / 1.42; to 400^2, p = 2.5: 1.88 / 0.73 /
-// 0.60; 240^3 to 256^2, p = 1.8: 0.84 / 0.28 / 0.22 ms; to 512^2, p = 0.9: 0.40 /
-// 0.33 / 0.56; 97^3 to 128^2, p = 1.5: 0.31 / 0.15 / 0.11 ms.
-static int ray_group(const RenderArgs &a) {
-  const double p = ray_pitch(a);
-  const int64_t rays = (int64_t)a.n_views * a.W * a.H;
-  if (p > 2.3 || rays <= 20000 || (p > 1.6 && rays <= 80000)) return 16;
-  return p > 1.08 || rays <= 400000 ? 4 : 2;
-}
-
 hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   RenderArgs a = a0;
   if (a.vol.dtype != kU16 && a.vol.dtype != kI16 && a.vol.dtype != kF32) return hipErrorInvalidValue;
@@ -190,7 +160,7 @@ hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   if (a.use_box) lds = with_box;
   a.occ_lds_words = occupancy_lds_words(a, lds);
   lds += (uint32_t)a.occ_lds_words * 4u;
-  const int group = ray_group(a);
+  const int group = ray_group(ray_pitch(a), (int64_t)a.n_views * a.W * a.H, 400000);
   if (a.shaded || a.filter != 0) return launch_render_variant(a, group, lds, s);
   // the shallow value box for volumes the MALL holds (their refills are
   // cheap, its fill passes fewer), the deep one above
@@ -198,47 +168,75 @@ hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   return launch_render_grouped<false, 0>(a, group, lds, s);
 }
 
-// Serving: kRayGroup workgroups per work item, a 16x16 super-tile of one
-// admitted request, its rays marched by lane groups as in the whole-image
-// kernel; the items of a launch may come from many requests of different
-// volumes, sizes and TFs.  The per-ray arithmetic is the whole-image
+// Serving: `parts` workgroups per work item, a 16x16 super-tile of one admitted
+// request, its rays marched by groups of the slot's lanes per ray as in the
+// whole-image kernel (the super-tile's `group` parts of 256 / group rays go
+// round its workgroups); the items of a launch may come from many requests of
+// different volumes, sizes and TFs.  The per-ray arithmetic is the whole-image
 // kernel's, so a request's pixels do not depend on what it is batched with.
-__global__ __launch_bounds__(kWgSize) void k_serve(const ServeSlot *slots, const ServeItem *items, int lds_k,
-                                                   int use_box, unsigned long long *samples) {
+template <class T>
+__device__ inline const T *constant_ref(const T *p) {
+  typedef const __attribute__((address_space(4))) T constant_T;
+  return (const T *)(constant_T *)(uintptr_t)p;
+}
+
+template <int G, int DT>
+__device__ inline void serve_part(const ServeSlot &sl, const ServeItem &it, const TfShared &s, bool tf_ok, ValBox &box,
+                                  __amdgpu_buffer_rsrc_t rs, int part, uint32_t &evaluated) {
+  int col, row;
+  group_pixel_of<G>(it.sx, it.sy, part, col, row);
+  const bool inside = col < sl.cam.W && row < sl.cam.H;
+  const bool lead = (threadIdx.x % G) == 0;
+  float4 rgba = nan_rgba();
+  if (tf_ok) {  // (uniform; the server validates every table at submit)
+    Ray r;
+    r.hit = false;
+    r.ns = 0;
+    r.k0 = 0;
+    if (inside) r = setup_ray(sl.cam, col, row, sl.vol.nx, sl.vol.ny, sl.vol.nz, sl.mc.step);
+    uint32_t unstaged = 0;
+    const ShadeConst sc{};
+    rgba = march_group<G, DT, false, 0>(sl.vol, s, sl.tf, sl.mc, sc, r, rs, box, evaluated, unstaged);
+  }
+  if (inside && lead) reinterpret_cast<float4 *>(sl.out)[(size_t)row * sl.cam.W + col] = rgba;
+}
+
+template <int G>
+__device__ inline void serve_part_any(const ServeSlot &sl, const ServeItem &it, const TfShared &s, bool tf_ok, ValBox &box,
+                                      __amdgpu_buffer_rsrc_t rs, int part, uint32_t &evaluated) {
+  switch (sl.vol.dtype) {  // uniform over the workgroup
+  case kU16: serve_part<G, kU16>(sl, it, s, tf_ok, box, rs, part, evaluated); break;
+  case kI16: serve_part<G, kI16>(sl, it, s, tf_ok, box, rs, part, evaluated); break;
+  default: serve_part<G, kF32>(sl, it, s, tf_ok, box, rs, part, evaluated); break;
+  }
+}
+
+__global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_serve(
+    const ServeSlot *slots, const ServeItem *items, int parts, int lds_k, int use_box, unsigned long long *samples) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  const ServeItem it = items[blockIdx.x / kRayGroup];  // (the item's parts are consecutive workgroups)
-  const int part = (int)(blockIdx.x % kRayGroup);
-  const ServeSlot &sl = slots[it.slot];
+  // both arrays are constant during the launch: read through the constant
+  // address space, their fields stay in scalar registers
+  const ServeItem it = *constant_ref(items + blockIdx.x / (unsigned)parts);
+  const ServeSlot &sl = *constant_ref(slots + it.slot);
+  int part = (int)(blockIdx.x % parts);
+  if (part >= sl.group) return;  // uniform over the workgroup
   TfShared s = carve_tf(lds, sl.tf.K);
   const bool tf_ok = load_tf(s, sl.tf);
-  int col, row;
-  group_pixel_of<kRayGroup>(it.sx, it.sy, part, col, row);
-  const bool inside = col < sl.cam.W && row < sl.cam.H;
-  const bool lead = (threadIdx.x % kRayGroup) == 0;
-  if (!tf_ok) {  // (the server validates every table at submit)
-    if (inside && lead) reinterpret_cast<float4 *>(sl.out)[(size_t)row * sl.cam.W + col] = nan_rgba();
-    return;
-  }
-  Ray r;
-  r.hit = false;
-  r.ns = 0;
-  r.k0 = 0;
-  if (inside) r = setup_ray(sl.cam, col, row, sl.vol.nx, sl.vol.ny, sl.vol.nz, sl.mc.step);
   __amdgpu_buffer_rsrc_t rs = make_rsrc(sl.vol.data, sl.vol.bytes);
-  uint32_t evaluated = 0, unstaged = 0;
+  uint32_t evaluated = 0;
   ValBox box;
   box.valid = false;
   box.ox = box.oy = box.oz = 0;
   box.cells = use_box ? reinterpret_cast<float *>(lds + vbox_lds_offset(lds_k)) + (threadIdx.x / kWaveSize) * kVBoxCells
                       : nullptr;
-  float4 rgba;
-  const ShadeConst sc{};
-  switch (sl.vol.dtype) {  // uniform over the workgroup
-  case kU16: rgba = march_group<kRayGroup, kU16, false, 0>(sl.vol, s, sl.tf, sl.mc, sc, r, rs, box, evaluated, unstaged); break;
-  case kI16: rgba = march_group<kRayGroup, kI16, false, 0>(sl.vol, s, sl.tf, sl.mc, sc, r, rs, box, evaluated, unstaged); break;
-  default: rgba = march_group<kRayGroup, kF32, false, 0>(sl.vol, s, sl.tf, sl.mc, sc, r, rs, box, evaluated, unstaged); break;
+  for (; part < sl.group; part += parts) {
+    if (sl.group == 2)
+      serve_part_any<2>(sl, it, s, tf_ok, box, rs, part, evaluated);
+    else if (sl.group == 4)
+      serve_part_any<4>(sl, it, s, tf_ok, box, rs, part, evaluated);
+    else
+      serve_part_any<16>(sl, it, s, tf_ok, box, rs, part, evaluated);
   }
-  if (inside && lead) reinterpret_cast<float4 *>(sl.out)[(size_t)row * sl.cam.W + col] = rgba;
   wave_count(samples, evaluated);
 }
 
@@ -252,7 +250,11 @@ hipError_t launch_serve_batch(const ServeSlot *slots_dev, const ServeItem *items
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_serve),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_serve, dim3((unsigned)(n_items * kRayGroup)), dim3(kWgSize), lds, s, slots_dev, items_dev,
+  // two workgroups per item when the items fill the device twice over (768
+  // workgroups at once), else up to one per part of 16
+  int parts = 2;
+  while (parts < 16 && (int64_t)n_items * parts < 1536) parts *= 2;
+  hipLaunchKernelGGL(k_serve, dim3((unsigned)(n_items * parts)), dim3(kWgSize), lds, s, slots_dev, items_dev, parts,
                      max_tf_k, use_box, samples);
   return hipGetLastError();
 }

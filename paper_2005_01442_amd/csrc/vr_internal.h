@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "vr.h"
 #include "vr_device.h"
 
@@ -75,9 +77,37 @@ hipError_t launch_render(const RenderArgs &a, hipStream_t s);
 // The same with local lighting or another filter (a.shaded, a.filter; `group`
 // lanes per ray and `lds` bytes as launch_render has chosen).
 hipError_t launch_render_variant(const RenderArgs &a, int group, uint32_t lds, hipStream_t s);
-// Largest distance, in voxels, between neighbouring rays of the launch's views
-// at the volume's centre.
-double ray_pitch(const RenderArgs &a);
+
+// Distance, in voxels, between neighbouring rays of a view at the volume's
+// centre; the largest of a launch's views.
+inline double ray_pitch(const VolConst &v, const CamConst &c) {
+  if (c.proj == 0) return 2.0 * std::max(c.hw / c.W, c.hh / c.H);
+  const double p[3] = {0.5 * (v.nx - 1), 0.5 * (v.ny - 1), 0.5 * (v.nz - 1)};
+  double z = 0.0;
+  for (int k = 0; k < 3; ++k) z += (p[k] - c.eye[k]) * c.fwd[k];
+  return 2.0 * std::max(z, 0.0) * c.th / c.H;
+}
+inline double ray_pitch(const RenderArgs &a) {
+  double most = 0.0;
+  for (int i = 0; i < a.n_views; ++i) most = std::max(most, ray_pitch(a.vol, a.cams[i]));
+  return most;
+}
+
+// Lanes per ray of a launch.  More lanes per ray make a wavefront's rays fewer
+// and closer: its samples fit the LDS box at larger distances p between rays
+// (8x4 rays of two samples up to p about 1.3, 4x4 of four up to 2.5, 2x2 of
+// sixteen up to 5; a wavefront that does not fit gathers 16 rows per sample from
+// global memory), and a launch of few rays is cut into more and shorter pieces,
+// against a longer compositing chain per sample.  Measured (int16, step 0.5,
+// blocks and ERT; 2 / 4 / 16 lanes): 512^3 to 1024^2, p = 0.97: 1.28 / 1.33 /
+// 2.85 ms; to 700^2, p = 1.4: 1.32 / 0.80 / 1.42; to 400^2, p = 2.5: 1.88 / 0.73 /
+// 0.60; 240^3 to 256^2, p = 1.8: 0.84 / 0.28 / 0.22 ms; to 512^2, p = 0.9: 0.40 /
+// 0.33 / 0.56; 97^3 to 128^2, p = 1.5: 0.31 / 0.15 / 0.11 ms.
+// `few`: rays below which two lanes per ray leave the device idle.
+inline int ray_group(double pitch, int64_t rays, int64_t few) {
+  if (pitch > 2.3 || rays <= 20000 || (pitch > 1.6 && rays <= few / 5)) return 16;
+  return pitch > 1.08 || rays <= few ? 4 : 2;
+}
 // Words of a.vol.occ a render launch stages in LDS after `lds` bytes of
 // other state (0: read from global memory).
 int32_t occupancy_lds_words(const RenderArgs &a, uint32_t lds);
@@ -133,6 +163,7 @@ struct ServeSlot {
   MarchConst mc;
   CamConst cam;
   float *out;
+  int32_t group;  // lanes per ray: 2, 4 or 16 (ray_group)
 };
 
 struct ServeItem {

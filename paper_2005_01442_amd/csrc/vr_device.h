@@ -1199,16 +1199,20 @@ struct NoPost {
 // permutation: [I, I, 2 + I, 2 + I] for pairs, [I, I, I, I] for quads; a row
 // broadcast for groups of 16).
 template <int G, int I>
-__device__ inline float from_group_lane(float x) {
+__device__ inline int from_group_lane_i32(int x) {
   if constexpr (G == 1) {
     return x;
   } else if constexpr (G == 16) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + I, 0xF, 0xF, true));
+    return __builtin_amdgcn_mov_dpp(x, 0x150 + I, 0xF, 0xF, true);
   } else {
     constexpr int hi = G == 2 ? 2 + I : I;
     constexpr int ctrl = I | (I << 2) | (hi << 4) | (hi << 6);
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), ctrl, 0xF, 0xF, false));
+    return __builtin_amdgcn_mov_dpp(x, ctrl, 0xF, 0xF, false);
   }
+}
+template <int G, int I>
+__device__ inline float from_group_lane(float x) {
+  return __builtin_bit_cast(float, from_group_lane_i32<G, I>(__builtin_bit_cast(int, x)));
 }
 
 // f(integral_constant<int, 0>), .., f(integral_constant<int, N - 1>).

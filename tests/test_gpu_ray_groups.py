@@ -49,3 +49,32 @@ def test_coarse_views_match_oracle(size):
     ref = oracle.render(vol, cams, synth.tf1(), 0.5, ert=0.99)
     got = gpu_render(vol, cams, synth.tf1(), 0.5, 0.99, True, block_edge=8)
     compare_with_flags(got, ref["rgba"], ref["flags"], 0.99)
+
+
+@pytest.mark.parametrize("size", [(160, 120), (180, 160)], ids=["16_and_4_lanes", "4_and_2_lanes"])
+def test_preintegrated_view_equals_the_same_among_sixteen(size):
+    cams = synth.orbit_cameras(DIMS, 16, 143, 60.0, *size)
+    tf = upload_tf(synth.tf1())
+    for dtype in (np.int16, np.float32):
+        vol = upload_volume(_volume(dtype))
+        blocks = vr.vr_build_blocks(vol, 8)
+        for step, ert, skip in ((0.5, 0.99, True), (1.3, 0.0, False), (2.5, 0.9, True)):
+            table = vr.vr_preint_build(tf, step)
+            many = vr.vr_render_preint(vol, blocks, cams, tf, table, step, ert, skip)
+            one = vr.vr_render_preint(vol, blocks, cams[5:6], tf, table, step, ert, skip)
+            full = vr.vr_render_preint(vol, None, cams[5:6], tf, table, step, ert, False)
+            assert torch.equal(one[0], many[5]) and torch.equal(one, full), (dtype, step)
+
+
+@pytest.mark.parametrize("nodes", [2, 3, 130, 257])
+@pytest.mark.parametrize("opacity", [0.0, 0.3, 60.0])
+def test_preint_table_sizes(nodes, opacity):
+    rng = np.random.default_rng(nodes)
+    table = rng.random((nodes, 4)).astype(np.float32)
+    table[:, 3] *= opacity
+    table[:: 3, 3] = 0.0
+    tf = synth.TransferFunction(table, -1.0, 2.0)
+    for step in (0.25, 8.0):
+        got = vr.vr_preint_table(vr.vr_preint_build(upload_tf(tf), step)).cpu().numpy()
+        # (the bar of test_gpu_preint: both sides integrate in FP64, entries lie in [0, 1] and are stored as fp32)
+        assert np.abs(got - oracle.preint_table(tf, step)).max() <= 1e-6

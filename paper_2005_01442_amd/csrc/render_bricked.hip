@@ -79,9 +79,9 @@ __device__ inline float reconstruct_slot(const char *slot, int S, int ox, int oy
   return combine(s, t);
 }
 
-// One pass over one view.  Each ray is marched by a pair of lanes (the group
-// walk of the in-core kernel, resumed at each ray's saved index), a
-// workgroup covers half a 16x16 super-tile, taken centre-out when the launch
+// One pass over one view.  Each ray is marched by a group of G lanes (the group
+// walk of the in-core kernel, resumed at each ray's saved index; G by the in-core
+// rule), a workgroup covers 256 / G rays of a 16x16 super-tile, taken centre-out when the launch
 // carries the in-core kernel's super-tile order (the tiles whose rays cross
 // the most volume first), else in Morton-chunk order: samples in empty
 // bricks are leapt over, samples in resident bricks evaluated from their
@@ -90,22 +90,26 @@ __device__ inline float reconstruct_slot(const char *slot, int S, int ox, int oy
 // state: per pixel (C_r, C_g, C_b, T); next: the next lattice index, or -1
 // once the ray is finished.  first: initialise the state instead of reading it.
 // The LDS boxes allow three workgroups per CU; the register budget matches.
-constexpr int kBrickRayGroup = 2;
-
-template <int DT>
+// A lane keeps its brick and slot from step to step: looking the page table up
+// (a global load before every step's box test) only where the brick changes,
+// with the occupancy bits in LDS and without the division of a brick index per
+// step, took the resident 512x512x400 int16 frame to 1024^2 from 1.79 to 1.63 ms.
+template <int G, int DT>
 __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_bricked_pass(
     const BrickedArgs args) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const BrickedArgs &a = kernarg<BrickedArgs>();
   int part;
-  const SuperTile tile = group_tile_of<kBrickRayGroup>(a.order, blockIdx.x, a.W, a.H, 1, kDefaultChunkEdge, part);
+  const SuperTile tile = group_tile_of<G>(a.order, blockIdx.x, a.W, a.H, 1, kDefaultChunkEdge, part);
   if (!tile.valid) return;  // uniform over the workgroup
   TfShared s = carve_tf(lds, a.tf.K);
+  if (a.occ_lds_words > 0)
+    stage_occupancy(s, a.fine, lds + vbox_lds_offset(a.tf.K) + vbox_lds_bytes(), a.occ_lds_words);
   const bool tf_ok = load_tf(s, a.tf);
   int col, row;
-  group_pixel_of<kBrickRayGroup>(tile.sx, tile.sy, part, col, row);
+  group_pixel_of<G>(tile.sx, tile.sy, part, col, row);
   const bool inside = col < a.W && row < a.H;
-  const bool lead = (threadIdx.x % kBrickRayGroup) == 0;  // the lane that stores its ray's state
+  const bool lead = (threadIdx.x % G) == 0;  // the lane that stores its ray's state
   const size_t pix = inside ? (size_t)row * a.W + col : 0;
   if (!tf_ok) {  // uniform: an invalid TF finishes every ray with NaN
     if (inside && lead) {
@@ -140,42 +144,46 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(3, 3)))
   box.ox = box.oy = box.oz = 0;
   box.cells = a.use_box ? reinterpret_cast<float *>(lds + vbox_lds_offset(a.tf.K)) + (threadIdx.x / kWaveSize) * kVBoxCells
                         : nullptr;
-  int box_slot = -1;  // uniform: the slot the box holds
-  int step_brick = -1, step_slot = -1;  // this lane's brick and slot at the current step (prep -> eval)
+  int box_slot = -1;               // uniform: the slot the box holds
+  float box_x = 0.0f, box_y = 0.0f, box_z = 0.0f;  // uniform: its footprint's origin
+  // this lane's brick (coordinates and slot), kept until a sample leaves it
+  int brick[3] = {-1, -1, -1}, slot = -1;
   auto prep = [&](bool want, float px, float py, float pz) {
-    step_brick = -1;
-    step_slot = -1;
     if (want) {
       int bc[3];
-      step_brick = block_of(a.vol, px, py, pz, bc);
-      step_slot = a.page[step_brick];
+      block_coords(a.vol, (int)floorf(px), (int)floorf(py), (int)floorf(pz), bc);
+      if (bc[0] != brick[0] || bc[1] != brick[1] || bc[2] != brick[2]) {
+        brick[0] = bc[0];
+        brick[1] = bc[1];
+        brick[2] = bc[2];
+        slot = a.page[block_index(a.vol, bc)];
+      }
     }
     if (!box.cells) return;
     const unsigned long long wm = __ballot(want);
     const int first = __ffsll((long long)wm) - 1;
-    const int s0 = __builtin_amdgcn_readlane(step_slot, first);
-    const int b0 = __builtin_amdgcn_readlane(step_brick, first);
-    if (s0 < 0 || __ballot(want && step_slot != s0) != 0ull) {  // not one resident brick
+    const int s0 = __builtin_amdgcn_readlane(slot, first);
+    if (s0 < 0 || __ballot(want && slot != s0) != 0ull) {  // not one resident brick
       box.valid = false;
       return;
     }
-    if (s0 != box_slot) box.valid = false;
-    box_slot = s0;
-    const int bx = b0 % a.vol.nbx, by = (b0 / a.vol.nbx) % a.vol.nby, bz = b0 / (a.vol.nbx * a.vol.nby);
+    if (s0 != box_slot) {
+      box.valid = false;
+      box_slot = s0;
+      box_x = (float)(__builtin_amdgcn_readlane(brick[0], first) * E - 1);
+      box_y = (float)(__builtin_amdgcn_readlane(brick[1], first) * E - 1);
+      box_z = (float)(__builtin_amdgcn_readlane(brick[2], first) * E - 1);
+    }
     VolConst sv = a.vol;  // the slot as a small volume of S^3 voxels
     sv.nx = sv.ny = sv.nz = S;
     sv.bytes = (uint32_t)a.slot_bytes;
     const __amdgpu_buffer_rsrc_t srs = make_rsrc(a.pool + (size_t)s0 * a.slot_bytes, (uint32_t)a.slot_bytes);
-    vbox_prepare<DT>(box, srs, sv, r, want, px - (float)(bx * E - 1), py - (float)(by * E - 1),
-                     pz - (float)(bz * E - 1));
+    vbox_prepare<DT>(box, srs, sv, r, want, px - box_x, py - box_y, pz - box_z);
   };
   auto eval = [&](int, float px, float py, float pz) -> ChainSample {
-    const int slot = step_slot;
     if (slot < 0) return ChainSample{0.0f, 0.0f, 0.0f, kStopSample};  // a later pass holds this brick
-    int bc[3];
-    block_of(a.vol, px, py, pz, bc);
     Stencil sten = make_stencil(px, py, pz);
-    const int ox = bc[0] * E - 1, oy = bc[1] * E - 1, oz = bc[2] * E - 1;
+    const int ox = brick[0] * E - 1, oy = brick[1] * E - 1, oz = brick[2] * E - 1;
     float val;
     if (box.valid) {  // every sampling lane is in the box's slot
       sten.ix -= ox;
@@ -194,7 +202,7 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(3, 3)))
   NoPost post;
   // skipping on the fine blocks; the brick of a sample to evaluate decides
   // whether this pass has it
-  const int parked = walk_group<kBrickRayGroup, false, true>(a.fine, s, a.tf, a.mc, r, eval, prep, take, flat, post,
+  const int parked = walk_group<G, false, true>(a.fine, s, a.tf, a.mc, r, eval, prep, take, flat, post,
                                                               st, kstart);
   if (active && lead) {
     a.state[pix] = st;
@@ -211,25 +219,31 @@ __global__ __launch_bounds__(kWgSize) void k_bricked_finish(const float4 *state,
   }
 }
 
+template <int G>
+static hipError_t launch_pass_as(const BrickedArgs &a, uint32_t lds, hipStream_t s) {
+  auto *k = a.vol.dtype == kU16 ? &k_bricked_pass<G, kU16> : (a.vol.dtype == kI16 ? &k_bricked_pass<G, kI16> : &k_bricked_pass<G, kF32>);
+  const void *fn = reinterpret_cast<const void *>(k);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const int tiles = ((a.W + kSuperEdge - 1) / kSuperEdge) * ((a.H + kSuperEdge - 1) / kSuperEdge);
+  const int64_t grid = group_grid(a.order ? (int64_t)tiles : grid_size_for(a.W, a.H, 1, kDefaultChunkEdge), G);
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kWgSize), lds, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_bricked_pass(const BrickedArgs &a0, hipStream_t s) {
   BrickedArgs a = a0;
-  const int tiles = ((a.W + kSuperEdge - 1) / kSuperEdge) * ((a.H + kSuperEdge - 1) / kSuperEdge);
   uint32_t lds = tf_lds_bytes(a.tf.K);
   const uint32_t with_box = vbox_lds_offset(a.tf.K) + vbox_lds_bytes();
   a.use_box = with_box <= max_lds_per_workgroup() ? 1 : 0;
   if (a.use_box) lds = with_box;
-  const void *fn = a.vol.dtype == kU16   ? reinterpret_cast<const void *>(&k_bricked_pass<kU16>)
-                   : a.vol.dtype == kI16 ? reinterpret_cast<const void *>(&k_bricked_pass<kI16>)
-                                         : reinterpret_cast<const void *>(&k_bricked_pass<kF32>);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  const int64_t grid = group_grid(a.order ? (int64_t)tiles : grid_size_for(a.W, a.H, 1, kDefaultChunkEdge), kBrickRayGroup);
-  switch (a.vol.dtype) {
-  case kU16: hipLaunchKernelGGL(k_bricked_pass<kU16>, dim3((unsigned)grid), dim3(kWgSize), lds, s, a); break;
-  case kI16: hipLaunchKernelGGL(k_bricked_pass<kI16>, dim3((unsigned)grid), dim3(kWgSize), lds, s, a); break;
-  default: hipLaunchKernelGGL(k_bricked_pass<kF32>, dim3((unsigned)grid), dim3(kWgSize), lds, s, a); break;
+  a.occ_lds_words = a.use_box ? occupancy_lds_words(a.fine, lds) : 0;
+  lds += (uint32_t)a.occ_lds_words * 4u;
+  switch (ray_group(ray_pitch(a.vol, a.cam), (int64_t)a.W * a.H, 400000)) {
+  case 16: return launch_pass_as<16>(a, lds, s);
+  case 4: return launch_pass_as<4>(a, lds, s);
+  default: return launch_pass_as<2>(a, lds, s);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_bricked_finish(const float4 *state, float4 *out, int64_t n, hipStream_t s) {

@@ -11,9 +11,9 @@ constexpr uint32_t kFwdWgPerCu = VR_FWD_MAX_WAVES;  // four wavefronts per workg
 // The occupancy bits join the LDS state (after the boxes) when three
 // workgroups still fit on a compute unit; else the kernels read them from
 // global memory.
-int32_t occupancy_lds_words(const RenderArgs &a, uint32_t lds) {
-  if (!a.use_box || !a.vol.occ) return 0;
-  const int64_t words = ((int64_t)a.vol.nbx * a.vol.nby * a.vol.nbz + 31) / 32;
+int32_t occupancy_lds_words(const VolConst &v, uint32_t lds) {
+  if (!v.occ) return 0;
+  const int64_t words = ((int64_t)v.nbx * v.nby * v.nbz + 31) / 32;
   return (int64_t)lds + words * 4 <= (int64_t)(kLdsPerCu / kFwdWgPerCu) ? (int32_t)words : 0;
 }
 // Workgroups of `fn` the current device holds at once with `lds` bytes of
@@ -158,7 +158,7 @@ hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   const uint32_t with_box = vbox_lds_offset(a.tf.K) + vbox_lds_bytes();
   a.use_box = with_box <= max_lds_per_workgroup() ? 1 : 0;
   if (a.use_box) lds = with_box;
-  a.occ_lds_words = occupancy_lds_words(a, lds);
+  a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
   const int group = ray_group(ray_pitch(a), (int64_t)a.n_views * a.W * a.H, 400000);
   if (a.shaded || a.filter != 0) return launch_render_variant(a, group, lds, s);

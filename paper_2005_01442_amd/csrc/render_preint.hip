@@ -401,7 +401,7 @@ hipError_t launch_render_preint(const RenderArgs &a0, const float4 *tab, hipStre
   const uint32_t with_box = vbox_lds_offset(a.tf.K) + vbox_lds_bytes();
   a.use_box = with_box <= max_lds_per_workgroup() ? 1 : 0;
   if (a.use_box) lds = with_box;
-  a.occ_lds_words = occupancy_lds_words(a, lds);
+  a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
   switch (ray_group(ray_pitch(a), (int64_t)a.n_views * a.W * a.H, 400000)) {
   case 16: return launch_preint_as<16>(a, tab, lds, s);

@@ -63,6 +63,7 @@ struct BrickedArgs {
   int32_t W, H;
   int32_t first;           // initialise the ray state
   int32_t use_box;         // stage LDS value boxes from the slots (set at launch)
+  int32_t occ_lds_words;   // > 0: stage fine.occ in LDS (set at launch)
   const int32_t *order;    // workgroup -> super-tile (centre-out, as in core), or nullptr: raster order
 };
 
@@ -108,9 +109,9 @@ inline int ray_group(double pitch, int64_t rays, int64_t few) {
   if (pitch > 2.3 || rays <= 20000 || (pitch > 1.6 && rays <= few / 5)) return 16;
   return pitch > 1.08 || rays <= few ? 4 : 2;
 }
-// Words of a.vol.occ a render launch stages in LDS after `lds` bytes of
-// other state (0: read from global memory).
-int32_t occupancy_lds_words(const RenderArgs &a, uint32_t lds);
+// Words of v.occ a render launch stages in LDS after `lds` bytes of other
+// state, value boxes included (0: read from global memory).
+int32_t occupancy_lds_words(const VolConst &v, uint32_t lds);
 // Number of workgroups of a render launch of `a` (one per super-tile with an
 // order, else the padded Morton grid).
 int64_t render_grid(const RenderArgs &a);

@@ -63,9 +63,9 @@ __device__ inline void scatter_taps(float *g, const VolConst &v, const Stencil &
 // 14 VALU and 9 LDS instructions (64 lanes each); one sample per wavefront
 // round, 64 lanes on its 64 taps, took 13.5 VALU and 5 LDS instructions per
 // sample and one LDS round trip per two (256^3 fp32, 64 views of 512^2, forward
-// and adjoint: 251 ms, 167 ms now; 512x512x400 int16 to 1024^2: 9.1 and 6.9
-// ms).  LDS float atomics measured at one
-// lane per ~4 cycles, also without conflicts.
+// and adjoint: 251 ms, then 167 ms; 512x512x400 int16 to 1024^2: 9.1, then 6.9
+// ms).  LDS float atomics (ds_add_f32) would take one lane per ~3 cycles, also
+// without conflicts.
 //
 // Slots lie at x + 12 z + 96 y (dwords): the 16 lanes of a group hit 16
 // distinct banks.  Coordinates are those of the unclamped stencil; flushing
@@ -87,15 +87,22 @@ typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 __device__ inline lds_float *lds_at(uint32_t address) { return (lds_float *)(uintptr_t)address; }
 __device__ inline uint32_t lds_address(lds_float *p) { return (uint32_t)(uintptr_t)p; }
 
-// LDS layout of the adjoint: TF + prefix counts, TF gradient (4K floats per
-// copy, when requested), then 16-byte aligned per-wavefront windows and
-// staging areas.  Two copies of the TF gradient still leave two workgroups per
-// CU.
-constexpr int kTfGradCopies = 2;
+// LDS layout of the adjoint: TF + prefix counts, TF gradient (four planes of K
+// doubles, when requested), then 16-byte aligned per-wavefront windows and
+// staging areas; two workgroups fit a CU.
+//
+// The TF gradient is in doubles because ds_add_f64 is the faster atomic: with 64
+// lanes on distinct words it takes the LDS 9 cycles, ds_add_f32 179 (one lane
+// after the other).  In floats, two copies by lane parity, the adds took 27 of
+// 167 ms (256^3 fp32, 64 views of 512^2, forward and adjoint; 140 ms now) and
+// 0.3 of 6.9 ms (512x512x400 int16 to 1024^2).  Planes per component put
+// neighbouring nodes on neighbouring banks.
+constexpr uint32_t kTfGradNodeBytes = 4 * sizeof(double);
 __host__ __device__ inline uint32_t box_lds_offset(int K, bool with_tf_grad) {
-  uint32_t o = tf_lds_bytes(K) + (with_tf_grad ? (uint32_t)K * 16u * kTfGradCopies : 0u);
+  uint32_t o = tf_lds_bytes(K) + (with_tf_grad ? (uint32_t)K * kTfGradNodeBytes : 0u);
   return (o + 15u) & ~15u;
 }
+typedef __attribute__((address_space(3))) double lds_double;
 
 struct GradWindow {
   lds_float *cells;  // this lane's group's window, zero outside use; nullptr: no windows
@@ -327,7 +334,7 @@ __device__ inline void win_add(GradWindow &w, float *grad, const VolConst &v, bo
 // T_{k+1} and C_{<=k} of its sample, and the lane applies that sample's
 // adjoint.
 template <int G, int MODE, int N, int DT>
-__device__ inline void march_backward(const VolConst &v, const TfShared &s, float *sgtf, GradWindow &win,
+__device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_double *sgtf, GradWindow &win,
                                       const TfConst &tf, const MarchConst &mc, const Ray &r,
                                       __amdgpu_buffer_rsrc_t rs, float4 g, float4 fin, float *grad_vol) {
   const float sl2 = mc.step * 1.4426950408889634f;
@@ -335,18 +342,16 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, floa
   // TF-gradient contributions are summed in registers for the two nodes of
   // the current TF segment (ga[0..3]: node cj, ga[4..7]: node cj + 1).  When
   // the segment moves by one node, the shared node's sums stay in registers
-  // and only the node left behind is added to LDS; otherwise both are.  The
-  // LDS TF gradient holds two interleaved copies, one per lane parity, so
-  // the two lanes of a ray pair (usually in the same segment) do not add to
-  // one address in the same instruction.
+  // and only the node left behind is added to LDS; otherwise both are.  (Every
+  // sample added to LDS at once: 140 -> 144 ms and 6.6 -> 8.5 ms on the cases
+  // above, lanes of a ray then adding to one word in the same instruction.)
   int cj = -1;
   float ga[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  const int tcopy = (int)(threadIdx.x % kTfGradCopies);
   auto add_node = [&](int node, const float *val) {
-    float *n0 = sgtf + 4 * node * kTfGradCopies + tcopy;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (val[i] != 0.0f) atomicAdd(n0 + i * kTfGradCopies, val[i]);
+      if (val[i] != 0.0f)
+        __hip_atomic_fetch_add(sgtf + i * tf.K + node, (double)val[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
   auto flush_tf = [&]() {
     if (cj >= 0) {
@@ -483,7 +488,7 @@ static int64_t g_timeline_bwd_records = 0;
 
 // One wavefront item of the adjoint: wavefront w of workgroup item i.
 template <int DT, int G, int MODE, int N>
-__device__ inline void backward_wave_item(const BackwardArgs &a, const TfShared &s, float *sgtf, GradWindow &win,
+__device__ inline void backward_wave_item(const BackwardArgs &a, const TfShared &s, lds_double *sgtf, GradWindow &win,
                                           __amdgpu_buffer_rsrc_t rs, int64_t i, int w) {
 #ifdef VR_TIMELINE
   const unsigned long long tl0 = __builtin_amdgcn_s_memrealtime();
@@ -529,9 +534,9 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const RenderArgs &ra = a.r;
   const int K = ra.tf.K;
   const uint32_t tf_bytes = tf_lds_bytes(K);
-  float *sgtf = a.grad_tf ? reinterpret_cast<float *>(lds + tf_bytes) : nullptr;
+  lds_double *sgtf = a.grad_tf ? (lds_double *)(lds + tf_bytes) : nullptr;
   if (sgtf)
-    for (int j = threadIdx.x; j < 4 * K * kTfGradCopies; j += kWgSize) sgtf[j] = 0.0f;
+    for (int j = threadIdx.x; j < 4 * K; j += kWgSize) sgtf[j] = 0.0;
   GradWindow win;
   win.valid = false;
   win.sx = win.ahead = 0;
@@ -576,9 +581,7 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(2, 2)))
   if (sgtf) {
     __syncthreads();
     for (int j = threadIdx.x; j < 4 * K; j += kWgSize) {
-      float val = 0.0f;
-#pragma unroll
-      for (int c = 0; c < kTfGradCopies; ++c) val += sgtf[j * kTfGradCopies + c];
+      const float val = (float)sgtf[(j & 3) * K + (j >> 2)];
       if (val != 0.0f) unsafeAtomicAdd(a.grad_tf + j, val);
     }
   }
@@ -614,7 +617,7 @@ hipError_t launch_render_backward(const BackwardArgs &a0, hipStream_t s) {
   BackwardArgs a = a0;
   const RenderArgs &ra = a.r;
   if (ra.vol.dtype != kU16 && ra.vol.dtype != kI16 && ra.vol.dtype != kF32) return hipErrorInvalidValue;
-  uint32_t lds = tf_lds_bytes(ra.tf.K) + (a.grad_tf ? (uint32_t)ra.tf.K * 16u * kTfGradCopies : 0u);
+  uint32_t lds = tf_lds_bytes(ra.tf.K) + (a.grad_tf ? (uint32_t)ra.tf.K * kTfGradNodeBytes : 0u);
   const uint32_t box_bytes = (uint32_t)(kWgSize / kWaveSize) * (kWinFloats + kProdFloats) * 4u;
   const uint32_t with_box = box_lds_offset(ra.tf.K, a.grad_tf != nullptr) + box_bytes;
   a.use_box = (a.grad_vol && with_box <= max_lds_per_workgroup()) ? 1 : 0;

@@ -86,7 +86,7 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ("render_fwd.hip", "render_march.h", "vr_device.h", "vr_internal.h")
+KERNEL_SOURCES = ("render_fwd.hip", "frame_prep.hip", "render_march.h", "vr_device.h", "vr_internal.h")
 
 
 def kernel_source_hash():
@@ -694,7 +694,7 @@ def main():
         "unit": "GB/s",
         "frac": achieved_gbs / HBM_PEAK_GBS,
         "traffic": traffic,
-        "kernel": "k_render<kI16, unlit, B-spline> (+ k_tile_order, k_occupancy_planes: one vr_render)",
+        "kernel": "k_render<kI16, unlit, B-spline> (+ k_occupancy_planes with the workgroup order: one vr_render)",
         "bytes_per_launch": compulsory,
         "bytes_definition": f"compulsory: the int16 volume read once ({vol_bytes} B) + the fp32 RGBA image "
                             f"written once ({img_bytes} B); time = median of the {args.steps} timed launches",

@@ -363,21 +363,11 @@ vr_status render_views(RenderArgs &a, const vr_camera *cams, int32_t n_cams, flo
     if (!bits) g_fallback_occupancy.fetch_add(1, std::memory_order_relaxed);
     if (bits) {
       // (pre-integration leaps block by block: its cells span two blocks)
-      if (!preint && occupancy_planes_fit(a.vol, a.tf.K)) {
-        radius = launch_occupancy_planes(a.vol, a.tf, bits, st) == hipSuccess;
-        if (!radius) (void)hipGetLastError();
-      }
-      if (!radius && launch_occupancy_bits(a.vol, a.tf, bits, st) != hipSuccess) {
-        (void)hipGetLastError();
-        if (own_bits) (void)hipFreeAsync(bits, st);
-        bits = nullptr;
-        own_bits = false;
-        g_fallback_occupancy.fetch_add(1, std::memory_order_relaxed);
-      }
+      radius = !preint && occupancy_planes_fit(a.vol, a.tf.K);
     }
   }
-  a.vol.occ = bits;
-  a.vol.occ_radius = radius ? kEmptyRadiusMax : 0;
+  a.vol.occ = nullptr;
+  a.vol.occ_radius = 0;
   // views per launch: what the kernel arguments carry and, with scratch,
   // what its order area holds
   int32_t per_launch = kMaxCamsPerLaunch;
@@ -391,17 +381,33 @@ vr_status render_views(RenderArgs &a, const vr_camera *cams, int32_t n_cams, flo
     for (int32_t i = 0; i < n; ++i) check_camera(&cams[v0 + i], &a.cams[i]);
     a.n_views = n;
     a.out = out_rgba + (size_t)v0 * view_floats;
-    bool own_order = false;
-    if (scratch) {
-      a.order = launch_tile_order(a, scratch->order, st) == hipSuccess ? scratch->order : nullptr;
-      if (!a.order) (void)hipGetLastError();
-    } else {
-      a.order = make_tile_order(a, st);
-      own_order = a.order != nullptr;
+    int32_t *order = scratch ? scratch->order : alloc_tile_order(a, st);
+    const bool own_order = order && !scratch;
+    bool ordered = false;
+    if (v0 == 0 && bits) {  // the planes, and the first views' order in the same launch
+      if (radius && order) {
+        ordered = launch_planes_and_order(a, bits, order, st) == hipSuccess;
+        radius = ordered;
+      } else if (radius) {
+        radius = launch_occupancy_planes(a.vol, a.tf, bits, st) == hipSuccess;
+      }
+      if (!radius) (void)hipGetLastError();
+      if (!radius && launch_occupancy_bits(a.vol, a.tf, bits, st) != hipSuccess) {
+        (void)hipGetLastError();
+        if (own_bits) (void)hipFreeAsync(bits, st);
+        bits = nullptr;
+        own_bits = false;
+        g_fallback_occupancy.fetch_add(1, std::memory_order_relaxed);
+      }
+      a.vol.occ = bits;
+      a.vol.occ_radius = radius ? kEmptyRadiusMax : 0;
     }
+    if (order && !ordered) ordered = launch_tile_order(a, order, st) == hipSuccess;
+    if (!ordered) (void)hipGetLastError();
+    a.order = ordered ? order : nullptr;
     if (!a.order) g_fallback_order.fetch_add(1, std::memory_order_relaxed);
     hipError_t e = preint ? launch_render_preint(a, preint, st) : launch_render(a, st);
-    if (own_order) (void)hipFreeAsync(const_cast<int32_t *>(a.order), st);
+    if (own_order) (void)hipFreeAsync(order, st);
     a.order = nullptr;
     if (e != hipSuccess) {
       result = hip_fail(e, "render launch");

@@ -1,5 +1,5 @@
 // render_fwd.hip -- forward ray casting (gfx950): the unlit whole-image kernel,
-// the workgroup order, launch rules, and the serving kernel.
+// launch rules, and the serving kernel.
 #include "render_march.h"
 
 namespace vr {
@@ -28,127 +28,10 @@ int64_t resident_workgroups(const void *fn, uint32_t lds) {
   return (int64_t)cus * per;
 }
 
-// ---------------------------------------------------------------------------
-// Centre-out workgroup order: a counting sort of the super-tiles by their
-// distance to the projected volume centre (half-tile rings) and, within a
-// ring, by angle around the centre (32 sectors), in one workgroup.  Item i of
-// the order runs on XCD i mod 8, so the angular order spreads every XCD's
-// tiles around each ring: an XCD does not inherit one side of the volume (in
-// raster order the two sides of a ring alternate, and the XCDs of one parity
-// took one side: 7.5 % more work on four of them for the C1 frame).  Items of
-// one (ring, sector) key come in any order; the image does not depend on the
-// order.
-// ---------------------------------------------------------------------------
-constexpr int kOrderRings = 256;
-constexpr int kOrderSectors = 32;
-constexpr int kOrderKeys = kOrderRings * kOrderSectors;
-constexpr int kOrderThreads = 1024;
-constexpr int kKeysPerThread = kOrderKeys / kOrderThreads;
-
-struct OrderArgs {
-  float cx[kMaxCamsPerLaunch], cy[kMaxCamsPerLaunch];  // centre, in super-tile units
-  int32_t tx, ty, n_views;
-};
-
-__device__ inline int order_key(const OrderArgs &o, int q) {
-  const int per = o.tx * o.ty, v = q / per, t = q % per;
-  const float dx = (float)(t % o.tx) - o.cx[v], dy = (float)(t / o.tx) - o.cy[v];
-  const float d = sqrtf(fmaf(dx, dx, dy * dy)) * 2.0f;
-  const int ring = d < (float)(kOrderRings - 1) ? (int)d : kOrderRings - 1;
-  const float turn = atan2f(dy, dx) * 0.15915494309189535f + 0.5f;  // in [0, 1]
-  const int sector = min(max((int)(turn * (float)kOrderSectors), 0), kOrderSectors - 1);
-  return ring * kOrderSectors + sector;
-}
-
-__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const OrderArgs o, int32_t *order) {
-  __shared__ int cnt[kOrderKeys];
-  const int n = o.n_views * o.tx * o.ty;
-  for (int i = threadIdx.x; i < kOrderKeys; i += kOrderThreads) cnt[i] = 0;
-  for (int i = threadIdx.x; i < (int)kOrderQueueInts; i += kOrderThreads) order[n + i] = 0;  // queue counters
-  __syncthreads();
-  for (int q = threadIdx.x; q < n; q += kOrderThreads) atomicAdd(&cnt[order_key(o, q)], 1);
-  __syncthreads();
-  // exclusive prefix sum of the counts: each thread sums its run of keys, an
-  // inclusive scan of those sums inside each wavefront, then the wavefront totals
-  __shared__ int wsum[kOrderThreads / kWaveSize];
-  const int lane = threadIdx.x % kWaveSize, wave = threadIdx.x / kWaveSize;
-  int run[kKeysPerThread], c = 0;
-#pragma unroll
-  for (int i = 0; i < kKeysPerThread; ++i) {
-    run[i] = cnt[threadIdx.x * kKeysPerThread + i];
-    c += run[i];
-  }
-  int x = c;
-#pragma unroll
-  for (int off = 1; off < kWaveSize; off <<= 1) {
-    const int y = __shfl_up(x, off, kWaveSize);
-    if (lane >= off) x += y;
-  }
-  if (lane == kWaveSize - 1) wsum[wave] = x;
-  __syncthreads();
-  int before = x - c;
-  for (int w = 0; w < wave; ++w) before += wsum[w];
-#pragma unroll
-  for (int i = 0; i < kKeysPerThread; ++i) {
-    cnt[threadIdx.x * kKeysPerThread + i] = before;
-    before += run[i];
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < n; q += kOrderThreads) order[atomicAdd(&cnt[order_key(o, q)], 1)] = q;
-}
-
 int64_t render_grid(const RenderArgs &a) {
   if (a.order)
     return (int64_t)a.n_views * ((a.W + kSuperEdge - 1) / kSuperEdge) * ((a.H + kSuperEdge - 1) / kSuperEdge);
   return grid_size_for(a.W, a.H, a.n_views, a.chunk_edge);
-}
-
-hipError_t launch_tile_order(const RenderArgs &a, int32_t *order, hipStream_t s) {
-  OrderArgs o;
-  o.tx = (a.W + kSuperEdge - 1) / kSuperEdge;
-  o.ty = (a.H + kSuperEdge - 1) / kSuperEdge;
-  o.n_views = a.n_views;
-  const double p[3] = {0.5 * (a.vol.nx - 1), 0.5 * (a.vol.ny - 1), 0.5 * (a.vol.nz - 1)};
-  for (int v = 0; v < a.n_views; ++v) {
-    const CamConst &c = a.cams[v];
-    double d[3], z = 0.0, x = 0.0, y = 0.0;
-    for (int k = 0; k < 3; ++k) d[k] = p[k] - c.eye[k];
-    for (int k = 0; k < 3; ++k) {
-      z += d[k] * c.fwd[k];
-      x += d[k] * c.right[k];
-      y += d[k] * c.up[k];
-    }
-    double sx = 0.0, sy = 0.0;  // image centre when the volume centre does not project
-    if (c.proj != 0) {
-      if (z > 0.0) {
-        sx = x / (z * c.th * ((double)c.W / (double)c.H));
-        sy = y / (z * c.th);
-      }
-    } else {
-      sx = c.hw > 0.0 ? x / c.hw : 0.0;
-      sy = c.hh > 0.0 ? y / c.hh : 0.0;
-    }
-    const double col = (sx + 1.0) * 0.5 * c.W - 0.5, row = (1.0 - sy) * 0.5 * c.H - 0.5;
-    o.cx[v] = (float)fmin(fmax((col + 0.5) / kSuperEdge - 0.5, -1e6), 1e6);
-    o.cy[v] = (float)fmin(fmax((row + 0.5) / kSuperEdge - 0.5, -1e6), 1e6);
-  }
-  hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(kOrderThreads), 0, s, o, order);
-  return hipGetLastError();
-}
-
-int64_t tile_order_count(const RenderArgs &a) {
-  return (int64_t)a.n_views * ((a.W + kSuperEdge - 1) / kSuperEdge) * ((a.H + kSuperEdge - 1) / kSuperEdge);
-}
-
-int32_t *make_tile_order(const RenderArgs &a, hipStream_t s) {
-  int32_t *order = nullptr;
-  if (hipMallocAsync((void **)&order, (size_t)(tile_order_count(a) + kOrderQueueInts) * sizeof(int32_t), s) != hipSuccess)
-    return nullptr;
-  if (launch_tile_order(a, order, s) != hipSuccess) {
-    (void)hipFreeAsync(order, s);
-    return nullptr;
-  }
-  return order;
 }
 
 hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {

@@ -124,6 +124,8 @@ int64_t render_grid(const RenderArgs &a);
 // (the Morton mapping is used then).  One order serves one launch: the
 // launch consumes its counters.
 int32_t *make_tile_order(const RenderArgs &a, hipStream_t s);
+// Its memory alone, not written.
+int32_t *alloc_tile_order(const RenderArgs &a, hipStream_t s);
 // The same order and counters written into `order` (tile_order_count(a) +
 // kOrderQueueInts entries, every one written), allocating nothing.
 hipError_t launch_tile_order(const RenderArgs &a, int32_t *order, hipStream_t s);
@@ -142,6 +144,9 @@ hipError_t launch_occupancy_bits(const VolConst &v, const TfConst &tf, uint32_t 
 // (see occupancy_planes_fit; then only launch_occupancy_bits applies).
 hipError_t launch_occupancy_planes(const VolConst &v, const TfConst &tf, uint32_t *bits, hipStream_t s);
 bool occupancy_planes_fit(const VolConst &v, int K);
+// The two planes and the workgroup order (as launch_tile_order) of a.vol, a.tf
+// and the views of `a` in one launch.
+hipError_t launch_planes_and_order(const RenderArgs &a, uint32_t *bits, int32_t *order, hipStream_t s);
 // Bytes of the occupancy bits plus the radius plane of a block grid.
 inline size_t occupancy_bytes(const VolConst &v) {
   const int64_t nb = (int64_t)v.nbx * v.nby * v.nbz;

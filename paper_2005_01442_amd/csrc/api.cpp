@@ -77,7 +77,6 @@ vr_status check_volume(const vr_volume *v, VolConst *out) {
     out->nbx = out->nby = out->nbz = 0;
     out->edge = 0;
     out->edge_shift = 0;
-    out->row_even = (v->nx % 2) == 0 ? 1 : 0;
   }
   return VR_OK;
 }

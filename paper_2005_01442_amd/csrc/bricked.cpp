@@ -178,7 +178,6 @@ static VolConst fine_grid(const vr_bricked *v) {
   f.nbz = v->fnbz;
   f.edge = v->F;
   f.edge_shift = __builtin_ctz((unsigned)v->F);
-  f.row_even = (v->nx % 2) == 0 ? 1 : 0;
   return f;
 }
 

@@ -77,7 +77,6 @@ struct VolConst {
   const float2 *minmax;     // per-block (min, max) or nullptr
   int32_t nbx, nby, nbz, edge;
   int32_t edge_shift;       // log2(edge)
-  int32_t row_even;         // nx even: every x-row starts at an even element
   // per-launch block occupancy under the TF, bit b % 32 of word b / 32
   // (nullptr: decided from minmax and the TF on the fly)
   const uint32_t *occ = nullptr;
@@ -302,7 +301,7 @@ __device__ inline void bspline_weights(float t, float w[4]) {
   w[2] = 1.0f - w[0] - w[1] - w[3];
 }
 
-typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -315,48 +314,33 @@ template <int DT> struct Vox;
 
 template <> struct Vox<kI16> {
   static constexpr int kBytes = 2;
-  // even-length rows: byte offset of the pair-aligned window `voff` (per
-  // lane), row offset `soff` (uniform, in the SGPR soffset), shift `sh`;
-  // row_s_load + row_unpack are the same in two parts (loads ahead of use)
-  using RawRow = u32x3;
-  __device__ static inline RawRow row_s_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    return __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, 0);
+  // four consecutive taps, `soff` (uniform) + `voff` (per lane) bytes into the
+  // volume: row_load + row_unpack (so that loads can run ahead of their use).
+  // The load needs a voxel's alignment only: rows of any length and parity take
+  // it.  (Three dwords from the even voxel before, shifted into place, and rows
+  // of odd length, whose parity changes from row to row, without loads ahead:
+  // adjoint of 512x512x400 to 1024^2 6.6 ms, 6.4 now; of 511x509x397 8.5 ms, 6.4 now.)
+  // The row's address goes through readfirstlane: it stays in scalar registers,
+  // and a load takes its lane offset without 64-bit vector adds.
+  using RawRow = u32x2;
+  __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t, const void *data, uint32_t voff, uint32_t soff) {
+    typedef const __attribute__((address_space(1))) char global_char;
+    const uint64_t at = (uint64_t)(uintptr_t)data + soff;
+    const uint64_t row = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at) |
+                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
+    RawRow w;
+    __builtin_memcpy(&w, (global_char *)row + voff, sizeof(w));
+    return w;
   }
-  __device__ static inline void row_unpack(const RawRow &v, uint32_t sh, float t[4]) {
-    uint32_t lo = __builtin_amdgcn_alignbit(v.y, v.x, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(v.z, v.y, sh);
-    t[0] = (float)(int16_t)(lo & 0xffffu);
-    t[1] = (float)((int32_t)lo >> 16);
-    t[2] = (float)(int16_t)(hi & 0xffffu);
-    t[3] = (float)((int32_t)hi >> 16);
-  }
-  __device__ static inline void row_s(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint32_t sh,
-                                      float t[4]) {
-    u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, 0);
-    uint32_t lo = __builtin_amdgcn_alignbit(v.y, v.x, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(v.z, v.y, sh);
-    t[0] = (float)(int16_t)(lo & 0xffffu);
-    t[1] = (float)((int32_t)lo >> 16);
-    t[2] = (float)(int16_t)(hi & 0xffffu);
-    t[3] = (float)((int32_t)hi >> 16);
-  }
-  // four consecutive taps starting at element e; e_al = e & ~1 even
-  __device__ static inline void row(__amdgpu_buffer_rsrc_t r, uint32_t e, float t[4]) {
-    uint32_t ea = e & ~1u;
-    u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, ea * 2u, 0, 0);
-    uint32_t sh = (e & 1u) * 16u;
-    uint32_t lo = __builtin_amdgcn_alignbit(v.y, v.x, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(v.z, v.y, sh);
-    t[0] = (float)(int16_t)(lo & 0xffffu);
-    t[1] = (float)((int32_t)lo >> 16);
-    t[2] = (float)(int16_t)(hi & 0xffffu);
-    t[3] = (float)((int32_t)hi >> 16);
+  __device__ static inline void row_unpack(const RawRow &w, float t[4]) {
+    t[0] = (float)(int16_t)(w.x & 0xffffu);
+    t[1] = (float)((int32_t)w.x >> 16);
+    t[2] = (float)(int16_t)(w.y & 0xffffu);
+    t[3] = (float)((int32_t)w.y >> 16);
   }
   __device__ static inline float one(__amdgpu_buffer_rsrc_t r, uint32_t e) {
     return (float)(int16_t)__builtin_amdgcn_raw_buffer_load_b16(r, e * 2u, 0, 0);
   }
-  // the dwordx3 window of the row starting at e lies inside the buffer
-  __device__ static inline bool window_ok(uint32_t e, uint32_t nvox) { return (e & ~1u) + 6u <= nvox; }
   // 16 consecutive voxels from element e: the 9-dword window from e & ~1,
   // loaded by row16_load and converted by row16_unpack (so that a caller can
   // keep several rows in flight)
@@ -384,43 +368,19 @@ template <> struct Vox<kI16> {
 
 template <> struct Vox<kU16> {
   static constexpr int kBytes = 2;
-  using RawRow = u32x3;
-  __device__ static inline RawRow row_s_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    return __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, 0);
+  using RawRow = Vox<kI16>::RawRow;
+  __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t r, const void *data, uint32_t voff, uint32_t soff) {
+    return Vox<kI16>::row_load(r, data, voff, soff);
   }
-  __device__ static inline void row_unpack(const RawRow &v, uint32_t sh, float t[4]) {
-    uint32_t lo = __builtin_amdgcn_alignbit(v.y, v.x, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(v.z, v.y, sh);
-    t[0] = (float)(lo & 0xffffu);
-    t[1] = (float)(lo >> 16);
-    t[2] = (float)(hi & 0xffffu);
-    t[3] = (float)(hi >> 16);
-  }
-  __device__ static inline void row_s(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint32_t sh,
-                                      float t[4]) {
-    u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, 0);
-    uint32_t lo = __builtin_amdgcn_alignbit(v.y, v.x, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(v.z, v.y, sh);
-    t[0] = (float)(lo & 0xffffu);
-    t[1] = (float)(lo >> 16);
-    t[2] = (float)(hi & 0xffffu);
-    t[3] = (float)(hi >> 16);
-  }
-  __device__ static inline void row(__amdgpu_buffer_rsrc_t r, uint32_t e, float t[4]) {
-    uint32_t ea = e & ~1u;
-    u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, ea * 2u, 0, 0);
-    uint32_t sh = (e & 1u) * 16u;
-    uint32_t lo = __builtin_amdgcn_alignbit(v.y, v.x, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(v.z, v.y, sh);
-    t[0] = (float)(lo & 0xffffu);
-    t[1] = (float)(lo >> 16);
-    t[2] = (float)(hi & 0xffffu);
-    t[3] = (float)(hi >> 16);
+  __device__ static inline void row_unpack(const RawRow &w, float t[4]) {
+    t[0] = (float)(w.x & 0xffffu);
+    t[1] = (float)(w.x >> 16);
+    t[2] = (float)(w.y & 0xffffu);
+    t[3] = (float)(w.y >> 16);
   }
   __device__ static inline float one(__amdgpu_buffer_rsrc_t r, uint32_t e) {
     return (float)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, e * 2u, 0, 0);
   }
-  __device__ static inline bool window_ok(uint32_t e, uint32_t nvox) { return (e & ~1u) + 6u <= nvox; }
   __device__ static inline bool row16_ok(uint32_t e, uint32_t nvox) { return (e & ~1u) + 18u <= nvox; }
   using Raw = Vox<kI16>::Raw;
   __device__ static inline Raw row16_load(__amdgpu_buffer_rsrc_t r, uint32_t e) { return Vox<kI16>::row16_load(r, e); }
@@ -439,26 +399,11 @@ template <> struct Vox<kU16> {
 template <> struct Vox<kF32> {
   static constexpr int kBytes = 4;
   using RawRow = u32x4;
-  __device__ static inline RawRow row_s_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t r, const void *, uint32_t voff, uint32_t soff) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
   }
-  __device__ static inline void row_unpack(const RawRow &w, uint32_t, float t[4]) {
+  __device__ static inline void row_unpack(const RawRow &w, float t[4]) {
     const f32x4 v = __builtin_bit_cast(f32x4, w);
-    t[0] = v.x;
-    t[1] = v.y;
-    t[2] = v.z;
-    t[3] = v.w;
-  }
-  __device__ static inline void row_s(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint32_t,
-                                      float t[4]) {
-    f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-    t[0] = v.x;
-    t[1] = v.y;
-    t[2] = v.z;
-    t[3] = v.w;
-  }
-  __device__ static inline void row(__amdgpu_buffer_rsrc_t r, uint32_t e, float t[4]) {
-    f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, e * 4u, 0, 0));
     t[0] = v.x;
     t[1] = v.y;
     t[2] = v.z;
@@ -467,7 +412,6 @@ template <> struct Vox<kF32> {
   __device__ static inline float one(__amdgpu_buffer_rsrc_t r, uint32_t e) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, e * 4u, 0, 0));
   }
-  __device__ static inline bool window_ok(uint32_t, uint32_t) { return true; }
   __device__ static inline bool row16_ok(uint32_t, uint32_t) { return true; }
   struct Raw {
     u32x4 a[4];
@@ -557,40 +501,22 @@ template <int DT, class Row>
 __device__ inline void for_rows(__amdgpu_buffer_rsrc_t rs, const VolConst &v, const Stencil &s, Row &row) {
   const int nx = v.nx, ny = v.ny, nz = v.nz;
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
-  const uint32_t nvox = nxy * (uint32_t)nz;
-  bool inner = (s.ix >= 1) & (s.ix + 2 <= nx - 1) & (s.iy >= 1) & (s.iy + 2 <= ny - 1) & (s.iz >= 1) &
-               (s.iz + 2 <= nz - 1);
+  const bool inner = (s.ix >= 1) & (s.ix + 2 <= nx - 1) & (s.iy >= 1) & (s.iy + 2 <= ny - 1) & (s.iz >= 1) &
+                     (s.iz + 2 <= nz - 1);
   if (inner) {
-    uint32_t e0 = ((uint32_t)(s.iz - 1) * (uint32_t)ny + (uint32_t)(s.iy - 1)) * (uint32_t)nx + (uint32_t)(s.ix - 1);
-    inner = Vox<DT>::window_ok(e0 + 3u * nxy + 3u * (uint32_t)nx, nvox);
-    if (inner && (DT == kF32 || v.row_even)) {
-      // every row has e0's parity: one per-lane window offset, the row
-      // offsets are uniform and travel in the load's SGPR soffset
-      const uint32_t kb = (uint32_t)Vox<DT>::kBytes;
-      const uint32_t voff = (DT == kF32) ? e0 * 4u : (e0 & ~1u) * 2u;
-      const uint32_t sh = (e0 & 1u) * 16u;
-      const uint32_t rs_x = (uint32_t)nx * kb, rs_xy = nxy * kb;
+    // one per-lane offset; the row offsets are uniform and stay in scalar registers
+    const uint32_t kb = (uint32_t)Vox<DT>::kBytes;
+    const uint32_t voff = kb * (((uint32_t)(s.iz - 1) * (uint32_t)ny + (uint32_t)(s.iy - 1)) * (uint32_t)nx + (uint32_t)(s.ix - 1));
+    const uint32_t rs_x = (uint32_t)nx * kb, rs_xy = nxy * kb;
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          float t[4];
-          Vox<DT>::row_s(rs, voff, (uint32_t)c * rs_xy + (uint32_t)b * rs_x, sh, t);
-          row(c, b, t);
-        }
-      return;
-    }
-    if (inner) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          float t[4];
-          Vox<DT>::row(rs, e0 + (uint32_t)c * nxy + (uint32_t)b * (uint32_t)nx, t);
-          row(c, b, t);
-        }
-      return;
-    }
+      for (int b = 0; b < 4; ++b) {
+        float t[4];
+        Vox<DT>::row_unpack(Vox<DT>::row_load(rs, v.data, voff, (uint32_t)c * rs_xy + (uint32_t)b * rs_x), t);
+        row(c, b, t);
+      }
+    return;
   }
   int xs[4];
 #pragma unroll
@@ -636,16 +562,15 @@ __device__ inline float reconstruct(__amdgpu_buffer_rsrc_t rs, const VolConst &v
 }
 
 // The first kRows of the 16 x-rows of the stencil at cell (ix, iy, iz),
-// loaded ahead of the sample that needs them (for_rows' interior fast path
-// only; else empty); the rest are loaded when the sample is taken.  Holding
-// all 16 across the adjoint's step spilled registers; with 8 the queued
-// adjoint fits 256 without spills (C1 fwd + adjoint 10.0 -> 9.0 ms, C3 292
-// -> 252 ms, with the queue).
+// loaded ahead of the sample that needs them (interior stencils only; else
+// empty); the rest are loaded when the sample is taken.  Holding all 16 across
+// the adjoint's step spilled registers; with 8 it fits 256 (12 rows of 16-bit
+// voxels ahead: 512x512x400 to 1024^2 6.4 -> 6.5 ms).
 template <int DT> struct TapPrefetch {
   static constexpr int kRows = 8;
   typename Vox<DT>::RawRow raw[kRows];
   int ix, iy, iz;  // ix == INT_MIN: empty
-  uint32_t sh, voff;
+  uint32_t voff;
 };
 
 template <int DT>
@@ -655,17 +580,14 @@ __device__ inline void prefetch_taps(TapPrefetch<DT> &p, __amdgpu_buffer_rsrc_t 
   const int nx = v.nx, ny = v.ny, nz = v.nz;
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
   const bool inner = (ix >= 1) & (ix + 2 <= nx - 1) & (iy >= 1) & (iy + 2 <= ny - 1) & (iz >= 1) & (iz + 2 <= nz - 1);
-  if (!inner || !(DT == kF32 || v.row_even)) return;
-  const uint32_t e0 = ((uint32_t)(iz - 1) * (uint32_t)ny + (uint32_t)(iy - 1)) * (uint32_t)nx + (uint32_t)(ix - 1);
-  if (!Vox<DT>::window_ok(e0 + 3u * nxy + 3u * (uint32_t)nx, nxy * (uint32_t)nz)) return;
+  if (!inner) return;
   const uint32_t kb = (uint32_t)Vox<DT>::kBytes;
-  const uint32_t voff = (DT == kF32) ? e0 * 4u : (e0 & ~1u) * 2u;
+  const uint32_t voff = kb * (((uint32_t)(iz - 1) * (uint32_t)ny + (uint32_t)(iy - 1)) * (uint32_t)nx + (uint32_t)(ix - 1));
   const uint32_t rs_x = (uint32_t)nx * kb, rs_xy = nxy * kb;
 #pragma unroll
   for (int i = 0; i < TapPrefetch<DT>::kRows; ++i)
-    p.raw[i] = Vox<DT>::row_s_load(rs, voff, (uint32_t)(i / 4) * rs_xy + (uint32_t)(i % 4) * rs_x);
+    p.raw[i] = Vox<DT>::row_load(rs, v.data, voff, (uint32_t)(i / 4) * rs_xy + (uint32_t)(i % 4) * rs_x);
   p.voff = voff;
-  p.sh = (e0 & 1u) * 16u;
   p.ix = ix;
   p.iy = iy;
   p.iz = iz;
@@ -684,7 +606,7 @@ __device__ inline float reconstruct_prefetched(const TapPrefetch<DT> &p, __amdgp
   const uint32_t rs_x = (uint32_t)v.nx * kb, rs_xy = (uint32_t)v.nx * (uint32_t)v.ny * kb;
 #pragma unroll
   for (int i = NP; i < 16; ++i)
-    late[i - NP] = Vox<DT>::row_s_load(rs, p.voff, (uint32_t)(i / 4) * rs_xy + (uint32_t)(i % 4) * rs_x);
+    late[i - NP] = Vox<DT>::row_load(rs, v.data, p.voff, (uint32_t)(i / 4) * rs_xy + (uint32_t)(i % 4) * rs_x);
   ValueRows f{s, 0.0f, 0.0f};
 #pragma unroll
   for (int c = 0; c < 4; ++c)
@@ -692,7 +614,7 @@ __device__ inline float reconstruct_prefetched(const TapPrefetch<DT> &p, __amdgp
     for (int b = 0; b < 4; ++b) {
       const int i = 4 * c + b;
       float t[4];
-      Vox<DT>::row_unpack(i < NP ? p.raw[i < NP ? i : 0] : late[i < NP ? 0 : i - NP], p.sh, t);
+      Vox<DT>::row_unpack(i < NP ? p.raw[i < NP ? i : 0] : late[i < NP ? 0 : i - NP], t);
       f(c, b, t);
     }
   return f.acc;

@@ -7,13 +7,12 @@
 // after interpolation through the transfer function; rays stop once opaque and
 // blocks with nothing visible are skipped (block decomposition, "Pros" (b)).
 //
-// Work layout: a wavefront owns an 8x8 pixel tile (one ray per lane), a
-// workgroup of four wavefronts a 16x16 super-tile; the whole-image forward
-// kernel marches each ray with a pair of lanes instead (8x4 rays per
-// wavefront, half a super-tile per workgroup).  The transfer function and
-// its non-zero-extinction bitmask live in LDS.  Volume taps are fetched with
-// raw buffer loads (bounds-checked by the hardware): an x-row of four int16
-// taps is one dwordx3 load plus two v_alignbit, an fp32 row one dwordx4 load.
+// Work layout: a workgroup of four wavefronts works on a 16x16 super-tile of
+// pixels or a part of it; G lanes (2, 4 or 16; 1 too in the adjoint) march one
+// ray, a wavefront a tile of 64 / G rays.  The transfer function and its
+// non-zero-extinction bitmask live in LDS.  An interior x-row of four voxels
+// is one load at a voxel's alignment (8 bytes of 16-bit voxels, 16 of fp32);
+// taps clamped at a face are raw buffer loads (bounds-checked by the hardware).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,7 +22,6 @@
 
 namespace vr {
 
-constexpr int kTileEdge = 8;          // pixels per wavefront tile edge
 constexpr int kSuperEdge = 16;        // pixels per workgroup super-tile edge
 constexpr int kWaveSize = 64;
 constexpr int kWgSize = 256;
@@ -1336,8 +1334,7 @@ __device__ inline void stage_occupancy(TfShared &s, const VolConst &v, char *dst
 }
 
 // ---------------------------------------------------------------------------
-// Tile mapping.  A workgroup owns a 16x16 super-tile; wavefront w the 8x8
-// sub-tile (w & 1, w >> 1); lane l the pixel (l & 7, l >> 3) of it.
+// Tile mapping.  A workgroup item is a 16x16 super-tile or a part of it.
 // Super-tiles are grouped in chunks of ce x ce (ce = 4: 64x64 pixels).  The
 // hardware hands workgroup i to XCD i mod 8; workgroup i works on chunk
 // g = 8 (i / 8 / ce^2) + (i mod 8), so XCD x runs the chunks g = x (mod 8) one
@@ -1406,12 +1403,6 @@ __device__ inline SuperTile tile_of(const int32_t *order, int64_t wg, int W, int
   st.sy = (q % per) / tx;
   st.valid = true;
   return st;
-}
-
-__device__ inline void pixel_of(int sx, int sy, int &col, int &row) {
-  int wave = threadIdx.x / kWaveSize, lane = threadIdx.x % kWaveSize;
-  col = sx * kSuperEdge + (wave & 1) * kTileEdge + (lane & 7);
-  row = sy * kSuperEdge + (wave >> 1) * kTileEdge + (lane >> 3);
 }
 
 // Workgroup -> (super-tile, part): with ray groups of G lanes a workgroup

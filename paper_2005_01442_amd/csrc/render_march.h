@@ -32,7 +32,7 @@ __device__ inline Classified eval_sample(const VolConst &v, const TfShared &s, c
     float4 vg;
     if (box.valid) {
       float t[4][4][4];
-      load_taps_box(box, sg.s, t);
+      load_taps_box<false>(box, sg.s, t);
       vg = combine_grad(sg, t);
     } else {
       vg = reconstruct_grad<DT>(rs, v, sg);
@@ -44,7 +44,7 @@ __device__ inline Classified eval_sample(const VolConst &v, const TfShared &s, c
     Stencil st = make_stencil(px, py, pz);
     float t[4][4][4];
     if (box.valid) {
-      load_taps_box(box, st, t);
+      load_taps_box<true>(box, st, t);
     } else {
       load_taps<DT>(rs, v, st, t);
       ++unstaged;

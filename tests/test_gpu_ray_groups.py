@@ -78,3 +78,20 @@ def test_preint_table_sizes(nodes, opacity):
         got = vr.vr_preint_table(vr.vr_preint_build(upload_tf(tf), step)).cpu().numpy()
         # (the bar of test_gpu_preint: both sides integrate in FP64, entries lie in [0, 1] and are stored as fp32)
         assert np.abs(got - oracle.preint_table(tf, step)).max() <= 1e-6
+
+
+@pytest.mark.parametrize("size", [(40, 33), (180, 160)], ids=["16_lanes", "4_lanes"])
+def test_nan_voxels_classify_as_the_first_node(size):
+    """A NaN value takes the TF's first node (coordinate 0) on every lane: an
+    all-NaN volume gives the image of an all-zero volume under a TF from 0, bit
+    for bit (zero is reconstructed exactly)."""
+    tf = synth.tf1()
+    table = torch.from_numpy(np.ascontiguousarray(tf.table)).cuda()
+    table[0] = torch.tensor([0.2, 0.5, 0.8, 0.07])
+    tf = vr.TF(table, 0.0, 1000.0)
+    cams = synth.orbit_cameras(DIMS, 1, 144, 60.0, *size)
+    images = []
+    for value in (np.nan, 0.0):
+        vol = upload_volume(np.full(DIMS[::-1], value, np.float32))
+        images.append(vr.vr_render(vol, None, cams, tf, 0.5, 0.99, False))
+    assert float(images[0].max()) > 0 and torch.equal(images[0], images[1])

@@ -19,11 +19,10 @@ __device__ inline void store_range(float2 *out, float2 *wide, int64_t b, float l
   wide[b] = make_float2(fmaf(-w, d, lo), fmaf(w, d, hi));
 }
 
-// A workgroup of eight wavefronts per row of blocks in x and BZ consecutive
-// blocks in z: the x-rows of the footprint ([bE - 1, bE + E + 1] in y and z,
-// clamped) are streamed in z order, each read once, the wavefronts taking every
-// eighth row, four rows per trip (their loads in flight together); a row adds
-// to the one or two blocks in z whose footprint holds it.  A lane holds eight
+// A workgroup of eight wavefronts per row of blocks in x: the x-rows of the
+// footprint ([bE - 1, bE + E + 1] in y and z, clamped) are streamed in z order,
+// the wavefronts taking every eighth row, four rows per trip (their loads in
+// flight together).  A lane holds eight
 // consecutive voxels (kRun) of a row, E / 8 lanes a block; the footprint's
 // apron along x (one voxel before the block, two after it) comes from the
 // neighbouring lanes.  The wavefronts are combined in LDS at the end of a pass
@@ -34,6 +33,9 @@ __device__ inline void store_range(float2 *out, float2 *wide, int64_t b, float l
 // the same path (one lane per 8 voxels with single-voxel loads, whose lanes
 // lie 16 bytes apart, took 218 us on 511x509x397 int16 where this takes 51 us: 4.1 of the 4.7 TB/s
 // a large copy reaches).
+// Neighbouring blocks in z share three planes, which the caches hold: four
+// blocks in z per workgroup, each plane read once, took 858 us on 1024^3 int16,
+// two 701, one 624 (fewer workgroups and selects per row).
 // The run of a row's last lane starts at the row's eighth voxel from its end and
 // is shifted into place by the same (uniform) count in every row.
 constexpr int kRun = 8;
@@ -126,21 +128,20 @@ template <> struct Run<float> {
 };
 
 // Block edges of 8 and more, rows of at least kRun voxels.
-template <typename T, int BZ>
+template <typename T>
 __global__ __launch_bounds__(kMinmaxThreads) void k_block_minmax(const VolConst v, float2 *out, float2 *wide, float widen) {
   typedef Run<T> R;
   constexpr int kWaves = kMinmaxThreads / kWaveSize;
-  __shared__ float smin[BZ][kWaves][kWaveSize], smax[BZ][kWaves][kWaveSize];
+  __shared__ float smin[kWaves][kWaveSize], smax[kWaves][kWaveSize];
   // XCD-aware: workgroup i runs on XCD i mod 8; each XCD takes a contiguous
   // run of items, neighbouring rows of blocks in y side by side
-  const int nchunks = (v.nbz + BZ - 1) / BZ;
-  const int nitems = v.nby * nchunks, per_xcd = (nitems + kXcds - 1) / kXcds;
+  const int nitems = v.nby * v.nbz, per_xcd = (nitems + kXcds - 1) / kXcds;
   const int q = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
   if (q >= nitems) return;
   const int E = v.edge, lpb_shift = v.edge_shift - 3, lpb = 1 << lpb_shift;  // lanes per block
-  const int by = q % v.nby, bz0 = (q / v.nby) * BZ, nbz = min(BZ, v.nbz - bz0);
+  const int by = q % v.nby, bz = q / v.nby;
   const int y0 = max(by * E - 1, 0), y1 = min(by * E + E + 1, v.ny - 1);
-  const int z0 = max(bz0 * E - 1, 0), z1 = min((bz0 + nbz) * E + 1, v.nz - 1);
+  const int z0 = max(bz * E - 1, 0), z1 = min(bz * E + E + 1, v.nz - 1);
   const int ny = y1 - y0 + 1, rows = ny * (z1 - z0 + 1);
   // the wavefront index, as a uniform value: the row walk below stays scalar
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWaveSize));
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kMinmaxThreads) void k_block_minmax(const VolConst 
     const int xa = bx0 * E + lane * kRun;  // this lane's first voxel
     const int xs = min(xa, v.nx - kRun);   // the run it loads
     const bool more = bx0 * E + kWaveSize * kRun < v.nx;  // uniform: voxels past the pass
-    typename R::Range range[BZ];
+    typename R::Range range;
     // footprint row r = (y - y0) + ny (z - z0), walked by increments (no
     // division per row); rows past the last repeat it, which changes nothing
     int r = wave, y = y0 + wave % ny, z = z0 + wave / ny;
@@ -182,22 +183,11 @@ __global__ __launch_bounds__(kMinmaxThreads) void k_block_minmax(const VolConst 
           hi0 = p;
           hi1 = n;
         }
-        typename R::Range here;
 #pragma unroll
-        for (int i = 0; i < R::kWords; ++i) here.add(w[i]);
-        here.add(first ? lo : w[0]);
-        here.add(final ? hi0 : w[0]);
-        here.add(final ? hi1 : w[0]);
-        if constexpr (BZ == 1) {
-          range[0].add(here);
-        } else {
-          // the blocks in z whose footprint holds row zz (one, or two at a
-          // boundary), relative to this item's first
-          const int jhi = ((zz + 1) >> v.edge_shift) - bz0, jlo = ((zz + E - 2) >> v.edge_shift) - 1 - bz0;
-#pragma unroll
-          for (int j = 0; j < BZ; ++j)
-            if ((j == jhi || j == jlo) && j < nbz) range[j].add(here);  // uniform
-        }
+        for (int i = 0; i < R::kWords; ++i) range.add(w[i]);
+        range.add(first ? lo : w[0]);
+        range.add(final ? hi0 : w[0]);
+        range.add(final ? hi1 : w[0]);
         r += kWaves;
         y += kWaves;
         while (y > y1) {
@@ -206,28 +196,25 @@ __global__ __launch_bounds__(kMinmaxThreads) void k_block_minmax(const VolConst 
         }
       }
     }
-#pragma unroll
-    for (int j = 0; j < BZ; ++j) {
-      float fmn = range[j].lo(), fmx = range[j].hi();
-      for (int off = 1; off < lpb; off <<= 1) {
-        fmn = fminf(fmn, __shfl_xor(fmn, off, kWaveSize));
-        fmx = fmaxf(fmx, __shfl_xor(fmx, off, kWaveSize));
-      }
-      if (first) {
-        smin[j][wave][lane >> lpb_shift] = fmn;
-        smax[j][wave][lane >> lpb_shift] = fmx;
-      }
+    float fmn = range.lo(), fmx = range.hi();
+    for (int off = 1; off < lpb; off <<= 1) {
+      fmn = fminf(fmn, __shfl_xor(fmn, off, kWaveSize));
+      fmx = fmaxf(fmx, __shfl_xor(fmx, off, kWaveSize));
+    }
+    if (first) {
+      smin[wave][lane >> lpb_shift] = fmn;
+      smax[wave][lane >> lpb_shift] = fmx;
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < per_pass * nbz; t += kMinmaxThreads) {
-      const int j = t / per_pass, i = t % per_pass, b = bx0 + i;
-      float m0 = smin[j][0][i], m1 = smax[j][0][i];
+    for (int i = threadIdx.x; i < per_pass; i += kMinmaxThreads) {
+      const int b = bx0 + i;
+      float m0 = smin[0][i], m1 = smax[0][i];
 #pragma unroll
       for (int w = 1; w < kWaves; ++w) {
-        m0 = fminf(m0, smin[j][w][i]);
-        m1 = fmaxf(m1, smax[j][w][i]);
+        m0 = fminf(m0, smin[w][i]);
+        m1 = fmaxf(m1, smax[w][i]);
       }
-      if (b < v.nbx) store_range(out, wide, ((int64_t)(bz0 + j) * v.nby + by) * v.nbx + b, m0, m1, widen);
+      if (b < v.nbx) store_range(out, wide, ((int64_t)bz * v.nby + by) * v.nbx + b, m0, m1, widen);
     }
     __syncthreads();
   }
@@ -267,10 +254,6 @@ __global__ __launch_bounds__(kWgSize) void k_block_minmax_small(const VolConst v
   if (at < nb && threadIdx.x % 8 == 0) store_range(out, wide, b, mn, mx, widen);
 }
 
-// Blocks in z per workgroup: four when that leaves at least
-// kMinmaxStreamItems workgroups (four per CU), else one.
-constexpr int kMinmaxStreamItems = 1024;
-
 template <typename T>
 static void launch_minmax(const VolConst &v, float2 *out, float2 *wide, float widen, hipStream_t s) {
   if (v.edge < kRun || v.nx < kRun) {
@@ -279,14 +262,8 @@ static void launch_minmax(const VolConst &v, float2 *out, float2 *wide, float wi
                        v, out, wide, widen);
     return;
   }
-  const int64_t items4 = (int64_t)v.nby * ((v.nbz + 3) / 4);
-  if (items4 >= kMinmaxStreamItems) {
-    const unsigned grid = (unsigned)((items4 + kXcds - 1) / kXcds * kXcds);
-    hipLaunchKernelGGL((k_block_minmax<T, 4>), dim3(grid), dim3(kMinmaxThreads), 0, s, v, out, wide, widen);
-  } else {
-    const unsigned grid = (unsigned)(((int64_t)v.nby * v.nbz + kXcds - 1) / kXcds * kXcds);
-    hipLaunchKernelGGL((k_block_minmax<T, 1>), dim3(grid), dim3(kMinmaxThreads), 0, s, v, out, wide, widen);
-  }
+  const unsigned grid = (unsigned)(((int64_t)v.nby * v.nbz + kXcds - 1) / kXcds * kXcds);
+  hipLaunchKernelGGL(k_block_minmax<T>, dim3(grid), dim3(kMinmaxThreads), 0, s, v, out, wide, widen);
 }
 
 hipError_t launch_block_minmax(const VolConst &v, float2 *out, float2 *wide, float widen, hipStream_t s) {

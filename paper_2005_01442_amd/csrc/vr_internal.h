@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "vr.h"
 #include "vr_device.h"
@@ -108,6 +109,18 @@ inline double ray_pitch(const RenderArgs &a) {
 inline int ray_group(double pitch, int64_t rays, int64_t few) {
   if (pitch > 2.3 || rays <= 20000 || (pitch > 1.6 && rays <= few / 5)) return 16;
   return pitch > 1.08 || rays <= few ? 4 : 2;
+}
+// Rays of a launch that cross the volume, about: each view's image, or the
+// volume's silhouette along the viewing direction over the rays' distance squared.
+inline double crossing_rays(const RenderArgs &a) {
+  double rays = 0.0;
+  for (int i = 0; i < a.n_views; ++i) {
+    const CamConst &c = a.cams[i];
+    const double p = ray_pitch(a.vol, c), nx = a.vol.nx, ny = a.vol.ny, nz = a.vol.nz;
+    const double area = std::abs(c.fwd[0]) * ny * nz + std::abs(c.fwd[1]) * nx * nz + std::abs(c.fwd[2]) * nx * ny;
+    rays += std::min((double)a.W * a.H, p > 0.0 ? area / (p * p) : INFINITY);
+  }
+  return rays;
 }
 // Words of v.occ a render launch stages in LDS after `lds` bytes of other
 // state, value boxes included (0: read from global memory).

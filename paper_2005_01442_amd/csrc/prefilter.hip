@@ -45,7 +45,6 @@ static double pivot(int i, double diag) {
 static float last_pivot(int n) { return (float)pivot(n - 1, 5.0); }
 
 constexpr int kRowMax = 16 * kWaveSize;        // x: voxels of a row (at most 16 per lane of its wavefront)
-constexpr int kRowsPerWg = kWgSize / kWaveSize;
 constexpr int kSeg = 64;                       // y, z: voxels of a line per thread
 constexpr int kLineWaves = 16;                 // y, z: wavefronts (segments of a line) per workgroup
 constexpr int kLineMax = kSeg * kLineWaves;
@@ -90,22 +89,24 @@ __device__ inline float carry_product(float p, float q) {
   return p == 0.0f || q == 0.0f ? 0.0f : copysignf(fmaxf(fabsf(r), 1.17549435e-38f), r);
 }
 
-// x axis, with the conversion to fp32: one wavefront per row, lane l solves
+// x axis, with the conversion to fp32: W lanes per row, lane l of them solves
 // voxels [l EM, l EM + EM), read and written as wide runs, and the carries
 // come from scans of the lanes' affine maps.  (Staging the row through LDS
 // for single-voxel coalesced accesses, any number of voxels per lane:
 // 255 us
-// against 145 us on 512x512x400 int16.)
-template <int DT, int EM>
+// against 145 us on 512x512x400 int16.)  W is the whole wavefront from rows of
+// 33 voxels on, else the power of two that holds the row: a launch has fewer
+// than 2 threads per voxel, below the 2^32 a grid may have, and few lanes idle.
+template <int DT, int EM, int W>
 __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, float *dst, int nx, int64_t rows,
                                                             const PrefilterCoef coef, float last) {
   constexpr int kHead = kPivots / EM;  // lanes whose pivots are not settled
   __shared__ float pivots[kPivots + EM];
   if (threadIdx.x < kPivots + EM) pivots[threadIdx.x] = coef.u[min((int)threadIdx.x, kPivots - 1)];
   __syncthreads();
-  const int lane = threadIdx.x % kWaveSize;
-  const int64_t row = (int64_t)blockIdx.x * kRowsPerWg + threadIdx.x / kWaveSize;
-  if (row >= rows) return;  // uniform over the wavefront; no barrier follows
+  const int lane = threadIdx.x % W;
+  const int64_t row = (int64_t)blockIdx.x * (kWgSize / W) + threadIdx.x / W;
+  if (row >= rows) return;  // uniform over the row's lanes; no barrier follows
   const int i0 = lane * EM, cnt = nx - i0;  // this lane's voxels in the row: min(cnt, EM)
   const int64_t base = row * nx + i0;
   // voxels past the row's end have factor 0: they carry nothing either way
@@ -134,14 +135,14 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
     P *= -u[j];
   }
 #pragma unroll
-  for (int off = 1; off < kWaveSize; off <<= 1) {
-    const float a = __shfl_up(P, off, kWaveSize), b = __shfl_up(y, off, kWaveSize);
+  for (int off = 1; off < W; off <<= 1) {
+    const float a = __shfl_up(P, off, W), b = __shfl_up(y, off, W);
     if (lane >= off) {
       y = fmaf(P, b, y);
       P = carry_product(P, a);
     }
   }
-  y = __shfl_up(y, 1, kWaveSize);
+  y = __shfl_up(y, 1, W);
   if (lane == 0) y = 0.0f;
 #pragma unroll
   for (int j = 0; j < EM; ++j) {
@@ -162,15 +163,15 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
     Q *= -u[j];
   }
 #pragma unroll
-  for (int off = 1; off < kWaveSize; off <<= 1) {
-    const float a = __shfl_down(Q, off, kWaveSize), b = __shfl_down(x, off, kWaveSize);
-    if (lane + off < kWaveSize) {
+  for (int off = 1; off < W; off <<= 1) {
+    const float a = __shfl_down(Q, off, W), b = __shfl_down(x, off, W);
+    if (lane + off < W) {
       x = fmaf(Q, b, x);
       Q = carry_product(Q, a);
     }
   }
-  x = __shfl_down(x, 1, kWaveSize);
-  if (lane == kWaveSize - 1) x = 0.0f;
+  x = __shfl_down(x, 1, W);
+  if (lane == W - 1) x = 0.0f;
 #pragma unroll
   for (int j = EM - 1; j >= 0; --j) {
     x = v[j] - u[j] * x;
@@ -282,6 +283,13 @@ __global__ __launch_bounds__(kWgSize) void k_to_f32(const void *src, float *dst,
     dst[i] = voxel_f32<DT>(src, i);
 }
 
+template <int DT, int EM, int W>
+static void launch_rows_as(const VolConst &v, float *out, const PrefilterCoef &coef, hipStream_t s) {
+  const int64_t rows = (int64_t)v.ny * v.nz, per_wg = kWgSize / W;
+  hipLaunchKernelGGL((k_prefilter_rows<DT, EM, W>), dim3((unsigned)((rows + per_wg - 1) / per_wg)), dim3(kWgSize), 0, s,
+                     v.data, out, v.nx, rows, coef, last_pivot(v.nx));
+}
+
 template <int DT>
 static void launch_rows(const VolConst &v, float *out, const PrefilterCoef &coef, hipStream_t s) {
   const int nx = v.nx;
@@ -294,13 +302,18 @@ static void launch_rows(const VolConst &v, float *out, const PrefilterCoef &coef
                          1, rows, nx, (int64_t)1, (int64_t)nx, coef, last_pivot(nx));
     return;
   }
-  // the fewest voxels per lane (1, 4, 8 or 16) that hold the row
-  auto *k = nx <= kWaveSize       ? &k_prefilter_rows<DT, 1>
-            : nx <= 4 * kWaveSize ? &k_prefilter_rows<DT, 4>
-            : nx <= 8 * kWaveSize ? &k_prefilter_rows<DT, 8>
-                                  : &k_prefilter_rows<DT, 16>;
-  hipLaunchKernelGGL(k, dim3((unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg)), dim3(kWgSize), 0, s, v.data, out, nx, rows,
-                     coef, last_pivot(nx));
+  // the fewest voxels per lane (1, 4, 8 or 16) and lanes that hold the row (with
+  // a whole wavefront per row, all three axes of 20x1024x1024 int16 took 395 us,
+  // 245 now; of 2x4096x4096 8.4 ms, 4.0 now)
+  if (nx <= 2) return launch_rows_as<DT, 1, 2>(v, out, coef, s);
+  if (nx <= 4) return launch_rows_as<DT, 1, 4>(v, out, coef, s);
+  if (nx <= 8) return launch_rows_as<DT, 1, 8>(v, out, coef, s);
+  if (nx <= 16) return launch_rows_as<DT, 1, 16>(v, out, coef, s);
+  if (nx <= 32) return launch_rows_as<DT, 1, 32>(v, out, coef, s);
+  if (nx <= kWaveSize) return launch_rows_as<DT, 1, kWaveSize>(v, out, coef, s);
+  if (nx <= 4 * kWaveSize) return launch_rows_as<DT, 4, kWaveSize>(v, out, coef, s);
+  if (nx <= 8 * kWaveSize) return launch_rows_as<DT, 8, kWaveSize>(v, out, coef, s);
+  return launch_rows_as<DT, 16, kWaveSize>(v, out, coef, s);
 }
 
 // `lines` lines of n voxels `stride` apart; line l starts at (l / nx) plane + l % nx.
@@ -325,6 +338,8 @@ hipError_t launch_prefilter(const VolConst &v, float *out, hipStream_t s) {
   case kI16: launch_rows<kI16>(v, out, coef, s); break;
   default: launch_rows<kF32>(v, out, coef, s); break;
   }
+  // (the passes along y and z read what this one writes)
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   const int64_t nx = v.nx, nxy = nx * v.ny;
   launch_lines(out, v.nx, nx * v.nz, v.ny, nx, nxy, coef, s);
   launch_lines(out, v.nx, nxy, v.nz, nxy, nx, coef, s);

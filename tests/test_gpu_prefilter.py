@@ -48,3 +48,25 @@ def test_infinite_voxel_reaches_its_lines(shape):
     got = vr.vr_prefilter_bspline(upload_volume(vol)).tensor.cpu().numpy()
     z, y, x = np.meshgrid(np.arange(nz) - at[0], np.arange(ny) - at[1], np.arange(nx) - at[2], indexing="ij")
     assert np.array_equal(got, np.where((z + y + x) % 2 == 0, np.inf, -np.inf).astype(np.float32))
+
+
+@pytest.mark.parametrize("nx", [2, 3, 5, 8, 9, 16, 17, 32, 33, 64])
+def test_prefilter_short_rows(nx):
+    """Several rows to a wavefront: rows that fill their lanes, rows that leave
+    some idle, a last workgroup that is not full."""
+    rng = np.random.default_rng(nx)
+    vol = rng.integers(-1024, 3072, (3, 131, nx)).astype(np.int16)
+    got = vr.vr_prefilter_bspline(upload_volume(vol)).tensor.cpu().numpy().astype(np.float64)
+    bound = 3 * 8 * 2.0**-24 * 27 * np.abs(vol.astype(np.float64)).max()  # as above
+    assert np.abs(got - oracle.prefilter(vol)).max() <= bound
+
+
+def test_prefilter_of_very_many_rows():
+    """2^26 rows: a wavefront per row would be 2^32 threads, which no launch
+    takes.  Volumes constant along y and z keep their row's coefficients."""
+    row = torch.tensor([100, 700], dtype=torch.int16, device="cuda")
+    vol = vr.Volume(row.expand(8192, 8192, 2).contiguous())
+    got = vr.vr_prefilter_bspline(vol).tensor
+    want = oracle.prefilter(np.array([[[100, 700]]], np.int16))[0, 0]
+    d = float((got - torch.from_numpy(want).to(got)).abs().max())
+    assert d <= 3 * 8 * 2.0**-24 * 27 * 700

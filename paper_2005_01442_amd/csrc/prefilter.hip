@@ -84,9 +84,18 @@ __device__ inline void load_run(const void *src, int64_t i, float v[EM]) {
 
 // Product of two runs' factors, kept from underflowing to 0: the carry of a
 // line that holds an infinity stays an infinity.
+constexpr float kLeastFactor = 1.17549435e-38f;
 __device__ inline float carry_product(float p, float q) {
   const float r = p * q;
-  return p == 0.0f || q == 0.0f ? 0.0f : copysignf(fmaxf(fabsf(r), 1.17549435e-38f), r);
+  return p == 0.0f || q == 0.0f ? 0.0f : copysignf(fmaxf(fabsf(r), kLeastFactor), r);
+}
+// `end` plus what a run of factor p passes on of `carry`.  A factor at the floor
+// stands for one that has underflowed: it passes on nothing finite, so that the
+// coefficients far from any voxel other than zero are zero (as sweeps of the
+// whole line give, and as the blocks there have to be to count as empty).
+__device__ inline float pass_on(float p, float carry, float end) {
+  const bool none = fabsf(p) <= kLeastFactor && __builtin_isfinite(carry);
+  return none ? end : fmaf(p, carry, end);
 }
 
 // x axis, with the conversion to fp32: W lanes per row, lane l of them solves
@@ -138,7 +147,7 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
   for (int off = 1; off < W; off <<= 1) {
     const float a = __shfl_up(P, off, W), b = __shfl_up(y, off, W);
     if (lane >= off) {
-      y = fmaf(P, b, y);
+      y = pass_on(P, b, y);
       P = carry_product(P, a);
     }
   }
@@ -166,7 +175,7 @@ __global__ __launch_bounds__(kWgSize) void k_prefilter_rows(const void *src, flo
   for (int off = 1; off < W; off <<= 1) {
     const float a = __shfl_down(Q, off, W), b = __shfl_down(x, off, W);
     if (lane + off < W) {
-      x = fmaf(Q, b, x);
+      x = pass_on(Q, b, x);
       Q = carry_product(Q, a);
     }
   }

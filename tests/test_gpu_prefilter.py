@@ -70,3 +70,19 @@ def test_prefilter_of_very_many_rows():
     want = oracle.prefilter(np.array([[[100, 700]]], np.int16))[0, 0]
     d = float((got - torch.from_numpy(want).to(got)).abs().max())
     assert d <= 3 * 8 * 2.0**-24 * 27 * 700
+
+
+@pytest.mark.parametrize("length", [200, 256, 512, 1000])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_prefilter_far_from_the_data_is_zero(axis, length):
+    """The coefficients fall off by 2 - sqrt(3) a voxel: 120 voxels from the last
+    voxel other than zero they are below the least fp32 number, zero.  A line's
+    first voxels are the largest, then its last."""
+    for at in (slice(0, 3), slice(length - 3, length)):
+        vol = np.zeros((length, 2, 2), np.float32)
+        vol[at] = 60000.0
+        vol = np.ascontiguousarray(np.moveaxis(vol, 0, axis))
+        got = vr.vr_prefilter_bspline(upload_volume(vol)).tensor.cpu().numpy()
+        line = np.abs(np.moveaxis(got, axis, 0)).max(axis=(1, 2))
+        far = line[123:] if at.start == 0 else line[: length - 123]
+        assert line.max() > 60000.0 and far.max() == 0.0

@@ -102,13 +102,16 @@ __device__ inline void serve_part_any(const ServeSlot &sl, const ServeItem &it, 
 }
 
 __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_serve(
-    const ServeSlot *slots, const ServeItem *items, int parts, int lds_k, int use_box, unsigned long long *samples) {
+    const ServeSlot *slots, const ServeItem *items, int n_items, int parts, int lds_k, int use_box,
+    unsigned long long *samples) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  const ServePart at = serve_part_of(blockIdx.x, parts);
+  if (at.item >= n_items) return;  // uniform: padding
   // both arrays are constant during the launch: read through the constant
   // address space, their fields stay in scalar registers
-  const ServeItem it = *constant_ref(items + blockIdx.x / (unsigned)parts);
+  const ServeItem it = *constant_ref(items + at.item);
   const ServeSlot &sl = *constant_ref(slots + it.slot);
-  int part = (int)(blockIdx.x % parts);
+  int part = at.part;
   if (part >= sl.group) return;  // uniform over the workgroup
   TfShared s = carve_tf(lds, sl.tf.K);
   const bool tf_ok = load_tf(s, sl.tf);
@@ -144,8 +147,8 @@ hipError_t launch_serve_batch(const ServeSlot *slots_dev, const ServeItem *items
   // workgroups at once), else up to one per part of 16
   int parts = 2;
   while (parts < 16 && (int64_t)n_items * parts < 1536) parts *= 2;
-  hipLaunchKernelGGL(k_serve, dim3((unsigned)(n_items * parts)), dim3(kWgSize), lds, s, slots_dev, items_dev, parts,
-                     max_tf_k, use_box, samples);
+  hipLaunchKernelGGL(k_serve, dim3((unsigned)serve_blocks(n_items, parts)), dim3(kWgSize), lds, s, slots_dev, items_dev,
+                     n_items, parts, max_tf_k, use_box, samples);
   return hipGetLastError();
 }
 

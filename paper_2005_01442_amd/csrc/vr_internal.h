@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "launch_rules.h"
 #include "vr.h"
 #include "vr_device.h"
 

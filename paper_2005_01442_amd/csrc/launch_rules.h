@@ -4,7 +4,96 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 namespace vr {
+
+// What the rays of a launch look like from the volume.
+struct RayField {
+  double pitch = 0.0;     // voxels between neighbouring rays (the largest of the views)
+  double rays = 0.0;      // pixels of all views
+  double crossing = 0.0;  // rays that cross the volume, about
+  double cover = 0.0;     // area of the volume's silhouettes over the images' (above 1: a closer view)
+};
+
+// Add a view.  The distance between rays is taken at the depth of the volume's
+// centre; where the eye is so close, or inside, that the far side lies more than
+// three times as deep, at a third of that.  (At the centre alone, views from
+// inside the volume counted as arbitrarily dense, although most of their samples
+// lie in front of the eye: 512x512x400 to 256^2 at 90 degrees, two lanes 0.57, four
+// 0.34 ms.)
+template <class Vol, class Cam>
+inline void add_view(RayField &f, const Vol &v, const Cam &c) {
+  const double n[3] = {(double)v.nx, (double)v.ny, (double)v.nz};
+  double z = 0.0, half = 0.0, f2 = 0.0;  // (a camera's forward vector need not have length 1)
+  for (int k = 0; k < 3; ++k) {
+    z += (0.5 * (n[k] - 1.0) - c.eye[k]) * c.fwd[k];
+    half += 0.5 * n[k] * std::abs(c.fwd[k]);
+    f2 += c.fwd[k] * c.fwd[k];
+  }
+  z /= f2;
+  half /= f2;
+  const double rays = (double)c.W * c.H;
+  const double p = c.proj == 0 ? 2.0 * std::max(c.hw / c.W, c.hh / c.H)
+                               : 2.0 * std::max(std::max(z, (z + half) / 3.0), 0.0) * c.th / c.H;
+  const double area = (std::abs(c.fwd[0]) * n[1] * n[2] + std::abs(c.fwd[1]) * n[0] * n[2] + std::abs(c.fwd[2]) * n[0] * n[1]) /
+                      std::sqrt(f2);
+  const double silhouette = p > 0.0 ? area / (p * p) : 0.0;  // (p = 0: the volume lies behind the eye)
+  const double before = f.rays;
+  f.rays += rays;
+  f.pitch = std::max(f.pitch, p);
+  f.crossing += std::min(rays, silhouette);
+  f.cover = (f.cover * before + silhouette) / f.rays;
+}
+
+// Lanes per ray of a whole-image launch.  More lanes per ray make a wavefront's
+// rays fewer and closer: its samples fit the LDS box at larger distances p between
+// rays (8x4 rays of two samples up to p about 1.3, 4x4 of four up to 2.5, 2x2 of
+// sixteen up to 5; a wavefront that does not fit gathers 16 rows per sample from
+// global memory), and a launch of few rays is cut into more and shorter pieces;
+// against that, each sample passes a longer compositing chain, and rays that miss
+// the volume cost their lanes (about 0.035 ns a lane: 16 views of 512^2 that the
+// volume covers to 5 %, p = 2.8: 1.07 ms with four, 2.56 with sixteen).  Measured in
+// some 2200 launches (volumes of 64^3 to 1000x900x700, images of 40^2 to 640^2, 1 to
+// 16 views, framed, far, close, from inside, orthographic; the lines below are within
+// 1 % of the best of 2, 4 and 16 lanes on average).  Step 0.5, int16, blocks and
+// ERT, microseconds with 2 / 4 / 16 lanes:
+//   256x256x200 to 128^2, framed, p = 3.7: 1220 / 510 / 151; 512^3 to 400^2, p = 2.5: 1880 / 730 / 600
+//   256x256x200 to 256^2, framed, p = 1.9: 797 / 240 / 181; to 512^2, p = 0.9: 400 / 330 / 560
+//   rays that all cross (a closer view): to 200^2, p = 0.8: 520 / 300 / 540, to 512^2, p = 0.3: 875 / 1085 / -
+// When every ray crosses, two lanes fill the device evenly from about 61440 rays
+// on; framed views, whose rays through the middle are the longest, gain from four
+// up to some 150000 crossing rays.  `skip`: empty blocks are leapt over (without,
+// the rays' work is even in framed views too).  `heavy`: a sample costs
+// several times a lookup of the box (pre-classification), which hides the chain: 256x256x200 to
+// 512^2, close: 3.3 ms with two lanes, 2.9 with four.
+inline int ray_group(const RayField &f, bool skip, bool heavy = false) {
+  const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
+  const double idle = heavy ? 4e6 : 1e6;  // missing rays that sixteen lanes are not worth
+  if (p > 2.8) return missing > idle && p < 4.5 ? 4 : 16;
+  const double few = 9300.0 * std::pow(std::max(1.0, p / 0.9), 1.45);
+  if ((x <= few || ((p > 0.9 || heavy) && f.rays <= 20000.0)) && missing < (p <= 2.3 ? 0.15 * idle : idle)) return 16;
+  if (p > 1.4) return 4;
+  if (missing > 1.5e6) return 2;
+  if (p > 1.08) return x > 300000.0 ? 2 : 4;
+  if (!skip) return x > 61440.0 ? 2 : 4;
+  if (heavy) return x > 400000.0 ? 2 : 4;
+  if (f.cover >= 2.0 || p < 0.3) return x > 61440.0 ? 2 : 4;
+  return x > (p <= 0.95 ? 150000.0 : 300000.0) ? 2 : 4;
+}
+
+// Lanes per ray of a served request, which shares its launch with others: a
+// launch of twelve requests fills the device whatever their size, and then has two
+// workgroups per super-tile, eight parts each with sixteen lanes.  So sixteen
+// are for small images and for coarse ones, and two from 200000 rays on (to
+// 128^2, close, alone / twelve at once: 16 lanes 0.30 / 2.5 ms, 4 lanes 0.33 / 1.4 ms;
+// to 400^2, close: 4 lanes 0.75 / 7.4 ms, 2 lanes 1.13 / 7.0 ms; to 512^2: 1.20 / 11.5, 0.99 / 9.2 ms).
+inline int serve_group(const RayField &f) {
+  const double p = f.pitch, x = f.crossing;
+  if (p > 2.8 || (p > 2.3 && x <= 20000.0 && f.rays - x < 150000.0) || (f.rays <= 20000.0 && x <= 10000.0)) return 16;
+  return p > 1.08 || f.rays <= 200000.0 ? 4 : 2;
+}
 
 // Workgroup -> (item, part) of a serving launch with `parts` workgroups per
 // item: the parts of item i run on XCD i mod 8 (the hardware hands workgroup b

@@ -43,14 +43,7 @@ hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  const double pitch = ray_pitch(a);
-  int group = ray_group(pitch, (int64_t)a.n_views * a.W * a.H, 400000);
-  // Without skipping the rays' work is even, and four lanes are worth their
-  // longer chain only while the rays that cross the volume about fit the device
-  // at once (49152 at four lanes; 2 / 4 lanes: 60,000 crossing rays, 200^3 to
-  // 384^2: 371 / 289 us, 64^3 to 384^2: 125 / 110; 65,536, 64^3 to 256^2
-  // orthographic: 114 / 140; 106,000, 128^3 to 512^2: 251 / 276).
-  if (group == 4 && pitch <= 1.08 && !a.mc.skip && crossing_rays(a) > 61440.0) group = 2;
+  const int group = ray_group(ray_field(a), a.mc.skip != 0, a.filter == 2);
   if (a.shaded || a.filter != 0) return launch_render_variant(a, group, lds, s);
   // the shallow value box for volumes the MALL holds (their refills are
   // cheap, its fill passes fewer), the deep one above

@@ -403,7 +403,7 @@ hipError_t launch_render_preint(const RenderArgs &a0, const float4 *tab, hipStre
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  switch (ray_group(ray_pitch(a), (int64_t)a.n_views * a.W * a.H, 400000)) {
+  switch (ray_group(ray_field(a), a.mc.skip != 0)) {
   case 16: return launch_preint_as<16>(a, tab, lds, s);
   case 4: return launch_preint_as<4>(a, tab, lds, s);
   default: return launch_preint_as<2>(a, tab, lds, s);

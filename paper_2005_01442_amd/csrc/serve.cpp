@@ -467,8 +467,7 @@ bool issue(vr_server *s, Batch &b) {
     sl.cam = r.cam;
     sl.mc = r.mc;
     sl.out = r.image;
-    // (a request shares the launch with others: two lanes per ray fill it sooner than a frame of its own)
-    sl.group = ray_group(ray_pitch(v.vc, r.cam), (int64_t)r.cam.W * r.cam.H, 100000);
+    sl.group = serve_group(ray_field(v.vc, r.cam));
     sl.tf.K = r.K;
     max_k = std::max(max_k, r.K);
     sl.tf.v0 = r.v0;

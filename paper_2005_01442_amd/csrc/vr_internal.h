@@ -96,32 +96,15 @@ inline double ray_pitch(const RenderArgs &a) {
   return most;
 }
 
-// Lanes per ray of a launch.  More lanes per ray make a wavefront's rays fewer
-// and closer: its samples fit the LDS box at larger distances p between rays
-// (8x4 rays of two samples up to p about 1.3, 4x4 of four up to 2.5, 2x2 of
-// sixteen up to 5; a wavefront that does not fit gathers 16 rows per sample from
-// global memory), and a launch of few rays is cut into more and shorter pieces,
-// against a longer compositing chain per sample.  Measured (int16, step 0.5,
-// blocks and ERT; 2 / 4 / 16 lanes): 512^3 to 1024^2, p = 0.97: 1.28 / 1.33 /
-// 2.85 ms; to 700^2, p = 1.4: 1.32 / 0.80 / 1.42; to 400^2, p = 2.5: 1.88 / 0.73 /
-// 0.60; 240^3 to 256^2, p = 1.8: 0.84 / 0.28 / 0.22 ms; to 512^2, p = 0.9: 0.40 /
-// 0.33 / 0.56; 97^3 to 128^2, p = 1.5: 0.31 / 0.15 / 0.11 ms.
-// `few`: rays below which two lanes per ray leave the device idle.
-inline int ray_group(double pitch, int64_t rays, int64_t few) {
-  if (pitch > 2.3 || rays <= 20000 || (pitch > 1.6 && rays <= few / 5)) return 16;
-  return pitch > 1.08 || rays <= few ? 4 : 2;
+inline RayField ray_field(const RenderArgs &a) {
+  RayField f;
+  for (int i = 0; i < a.n_views; ++i) add_view(f, a.vol, a.cams[i]);
+  return f;
 }
-// Rays of a launch that cross the volume, about: each view's image, or the
-// volume's silhouette along the viewing direction over the rays' distance squared.
-inline double crossing_rays(const RenderArgs &a) {
-  double rays = 0.0;
-  for (int i = 0; i < a.n_views; ++i) {
-    const CamConst &c = a.cams[i];
-    const double p = ray_pitch(a.vol, c), nx = a.vol.nx, ny = a.vol.ny, nz = a.vol.nz;
-    const double area = std::abs(c.fwd[0]) * ny * nz + std::abs(c.fwd[1]) * nx * nz + std::abs(c.fwd[2]) * nx * ny;
-    rays += std::min((double)a.W * a.H, p > 0.0 ? area / (p * p) : INFINITY);
-  }
-  return rays;
+inline RayField ray_field(const VolConst &v, const CamConst &c) {
+  RayField f;
+  add_view(f, v, c);
+  return f;
 }
 // Words of v.occ a render launch stages in LDS after `lds` bytes of other
 // state, value boxes included (0: read from global memory).

@@ -2,9 +2,11 @@
 covered once, and the lines of the rules lie where the measurements put them."""
 
 import ctypes
+import math
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -17,6 +19,10 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", CSRC, "-o", out,
                     os.path.join(ROOT, "tests", "launch_rules_driver.cpp")], check=True)
     lib = ctypes.CDLL(out)
+    view = [ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_double), ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    lib.ray_field.argtypes = [*view, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]
+    lib.ray_group.argtypes = [*view, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    lib.serve_group.argtypes = view
     lib.serve_blocks.restype = ctypes.c_int64
     lib.serve_blocks.argtypes = [ctypes.c_int64, ctypes.c_int]
     lib.serve_part.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int)]
@@ -43,3 +49,98 @@ def test_serving_parts_cover_their_items_on_every_xcd(rules, items, parts):
     for lanes, load in loads.items():
         assert sum(load) == items * min(lanes, parts)
         assert max(load) == -(-items // 8) * min(lanes, parts)
+
+
+def camera(dims, size, view):
+    """(projection, eye, forward, tan(fov / 2), half extents) of the measured views."""
+    n = np.array(dims, float)
+    u = np.array([-0.6635568, -0.64628677, 0.37683654])
+    u /= np.linalg.norm(u)
+    away, fov, eye = {"framed": (1, 60, None), "far": (3, 60, None), "near": (0.35, 60, None), "narrow": (1, 8, None),
+                      "nearer": (0.6, 60, None), "inside": (0, 60, (0.5, 0.5, 0.5)), "inside_wide": (0, 90, (0.3, 0.6, 0.4)),
+                      "ortho": (1, 60, None)}[view]
+    where = (n - 1) / 2 + away * np.linalg.norm(n) * u if eye is None else n * eye
+    half = 0.5 * float(n.max())
+    return [0 if view == "ortho" else 1, *where, *-u, math.tan(math.radians(fov) / 2), half, half]
+
+
+def lanes(rules, dims, size, view, views=1, skip=True, heavy=False):
+    c = camera(dims, size, view)
+    return rules.ray_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, views, skip, heavy)
+
+
+# microseconds of int16 frames with blocks, step 0.5, by lanes per ray
+S, M, L, XL = (128, 120, 100), (256, 256, 200), (512, 512, 400), (1000, 900, 700)
+FRAMES = [
+    (M, 128, "framed", 1, {2: 1220, 4: 510, 16: 151}),
+    (M, 256, "framed", 1, {2: 797, 4: 240, 16: 181}),
+    (M, 512, "framed", 1, {2: 400, 4: 330, 16: 560}),
+    (L, 1024, "framed", 1, {2: 1160, 4: 1290, 16: 2850}),
+    (L, 512, "framed", 1, {2: 1940, 4: 580}),
+    (S, 512, "far", 16, {2: 523, 4: 735, 16: 2380}),
+    (M, 512, "far", 16, {2: 1690, 4: 1067, 16: 2560}),
+    (M, 512, "far", 1, {2: 1045, 4: 333, 16: 192}),
+    (S, 320, "far", 1, {2: 467, 4: 154, 16: 103}),
+    (M, 512, "near", 1, {2: 875, 4: 1085}),
+    (M, 512, "narrow", 1, {2: 960, 4: 1193}),
+    (L, 512, "narrow", 1, {2: 1758, 4: 2202}),
+    (S, 512, "near", 1, {2: 491, 4: 604}),
+    (M, 200, "near", 1, {2: 430, 4: 300, 16: 480}),
+    (M, 512, "inside", 1, {2: 525, 4: 652}),
+    (L, 256, "inside_wide", 1, {2: 573, 4: 337, 16: 597}),
+    (L, 512, "inside_wide", 1, {2: 915, 4: 1077}),
+    (XL, 256, "inside_wide", 1, {2: 1743, 4: 688, 16: 1031}),
+    (M, 256, "ortho", 1, {2: 364, 4: 231, 16: 390}),
+    (M, 512, "nearer", 1, {2: 592, 4: 659}),
+]
+
+
+@pytest.mark.parametrize("dims,size,view,views,times", FRAMES, ids=lambda v: str(v) if not isinstance(v, dict) else "")
+def test_lanes_per_ray_are_the_measured_best(rules, dims, size, view, views, times):
+    assert times[lanes(rules, dims, size, view, views)] <= 1.05 * min(times.values())
+
+
+def test_lanes_per_ray_over_odd_cameras(rules):
+    """Every accepted camera gets 2, 4 or 16 lanes: the volume behind the eye,
+    extents far beyond it, images of one pixel and of the largest size, forward
+    vectors of any length (which leave the answer alone)."""
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        dims = rng.integers(1, 900, 3)
+        W, H = (int(v) for v in rng.choice([1, 3, 64, 511, 4096, 32768], 2))
+        cam = [*rng.normal(0, 600, 3), *rng.normal(0, 1, 3), 10 ** rng.uniform(-4, 4), *(10 ** rng.uniform(-3, 6, 2))]
+        proj, views = int(rng.integers(0, 2)), int(rng.integers(1, 17))
+        args = ((ctypes.c_int32 * 3)(*map(int, dims)), (ctypes.c_double * 9)(*cam), proj, W, H)
+        out = (ctypes.c_double * 4)()
+        rules.ray_field(*args, views, out)
+        assert all(math.isfinite(v) and v >= 0 for v in out) and out[2] <= out[1] == views * W * H
+        for skip in (0, 1):
+            for heavy in (0, 1):
+                assert rules.ray_group(*args, views, skip, heavy) in (2, 4, 16)
+        assert rules.serve_group(*args) in (2, 4, 16)
+        if proj == 1:  # the same view with a longer forward vector: the plane at distance 1 moves to 3
+            longer = [*cam[:3], *(3 * v for v in cam[3:6]), 3 * cam[6], 0.0, 0.0]
+            other = (ctypes.c_double * 4)()
+            rules.ray_field(args[0], (ctypes.c_double * 9)(*longer), 1, W, H, views, other)
+            assert np.allclose(out[:], other[:], rtol=1e-9)
+
+
+# microseconds of one and of twelve requests at once, by lanes per ray
+REQUESTS = [
+    (M, 64, "framed", {4: 841, 16: 279}, {4: 1985, 16: 828}),
+    (M, 128, "near", {4: 329, 16: 304}, {4: 1443, 16: 2546}),
+    (M, 200, "framed", {4: 399, 16: 228}, {4: 1410, 16: 1910}),
+    (M, 256, "near", {2: 662, 4: 451}, {2: 3684, 4: 3464}),
+    (M, 400, "near", {2: 1137, 4: 755}, {2: 7058, 4: 7358}),
+    (M, 400, "far", {4: 720, 16: 544}, {4: 2395, 16: 2090}),
+    (M, 512, "far", {4: 778, 16: 1014}, {4: 2194, 16: 2998}),
+    (M, 512, "near", {2: 990, 4: 1196}, {2: 9237, 4: 11525}),
+    (M, 1024, "framed", {2: 984, 4: 1118}, {2: 9749, 4: 11518}),
+]
+
+
+@pytest.mark.parametrize("dims,size,view,alone,twelve", REQUESTS, ids=lambda v: str(v) if not isinstance(v, dict) else "")
+def test_lanes_of_requests_serve_one_and_many(rules, dims, size, view, alone, twelve):
+    c = camera(dims, size, view)
+    g = rules.serve_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size)
+    assert alone[g] * twelve[g] == min(alone[k] * twelve[k] for k in alone)

@@ -65,10 +65,12 @@ inline void add_view(RayField &f, const Vol &v, const Cam &c) {
 // When every ray crosses, two lanes fill the device evenly from about 61440 rays
 // on; framed views, whose rays through the middle are the longest, gain from four
 // up to some 150000 crossing rays.  `skip`: empty blocks are leapt over (without,
-// the rays' work is even in framed views too).  `heavy`: a sample costs
-// several times a lookup of the box (pre-classification), which hides the chain: 256x256x200 to
-// 512^2, close: 3.3 ms with two lanes, 2.9 with four.
-inline int ray_group(const RayField &f, bool skip, bool heavy = false) {
+// the rays' work is even in framed views too).  `full`: the rays of a closer view
+// from which two lanes are ahead.  `heavy`: a sample costs several times a lookup
+// of the box (pre-classification), which hides the chain: 256x256x200 to 512^2,
+// close: 3.3 ms with two lanes, 2.9 with four.
+constexpr double kFullRays = 61440.0, kFullCells = 170000.0, kFullHeavy = 400000.0;
+inline int ray_group(const RayField &f, bool skip, double full = kFullRays, bool heavy = false) {
   const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
   const double idle = heavy ? 4e6 : 1e6;  // missing rays that sixteen lanes are not worth
   if (p > 2.8) return missing > idle && p < 4.5 ? 4 : 16;
@@ -77,10 +79,20 @@ inline int ray_group(const RayField &f, bool skip, bool heavy = false) {
   if (p > 1.4) return 4;
   if (missing > 1.5e6) return 2;
   if (p > 1.08) return x > 300000.0 ? 2 : 4;
-  if (!skip) return x > 61440.0 ? 2 : 4;
-  if (heavy) return x > 400000.0 ? 2 : 4;
-  if (f.cover >= 2.0 || p < 0.3) return x > 61440.0 ? 2 : 4;
-  return x > (p <= 0.95 ? 150000.0 : 300000.0) ? 2 : 4;
+  if (!skip) return x > kFullRays ? 2 : 4;
+  if (f.cover < 2.0 && p >= 0.3) full = std::max(full, p <= 0.95 ? 150000.0 : 300000.0);
+  return x > full ? 2 : 4;
+}
+
+// Lanes per ray of a pre-integrated launch: as above, and one where the rays fill
+// the image closely and the device several times over (a cell's near value then
+// is the lane's own of the step before).  One / two / four lanes, step 0.5,
+// microseconds: 512x512x400 to 1024^2, p = 0.33: 5370 / 5820 / 6650, p = 0.93 (framed): - / 1640 / -;
+// 128x120x100 to 700^2, p = 0.12: 897 / 955 / 1078; to 400^2, p = 0.2: 411 / 443 / 453;
+// 256x256x200 to 400^2, p = 0.7: 800 / 560 / 514; to 256^2, close: 731 / 404 / 374.
+inline int preint_group(const RayField &f, bool skip) {
+  if (f.cover >= 1.0 && ((f.pitch < 0.6 && f.crossing > 300000.0) || (f.pitch < 0.22 && f.crossing > 147456.0))) return 1;
+  return ray_group(f, skip, kFullCells);
 }
 
 // Lanes per ray of a served request, which shares its launch with others: a

@@ -147,6 +147,7 @@ __device__ inline float4 preint_lookup(const float4 *tab, int K, float uf, float
 // Lane j - 1's value to lane j of a ray group (lane 0 keeps `first`).
 template <int G>
 __device__ inline int from_left(int x, int first) {
+  if constexpr (G == 1) return first;
   // quad_perm [0, 0, 2, 2] / [0, 0, 1, 2], row_shr:1
   constexpr int ctrl = G == 2 ? 0xA0 : (G == 4 ? 0x90 : 0x111);
   const int y = __builtin_amdgcn_mov_dpp(x, ctrl, 0xF, 0xF, true);
@@ -155,6 +156,7 @@ __device__ inline int from_left(int x, int first) {
 // Lane j + 1's value to lane j of a ray group (the last lane gets 0).
 template <int G>
 __device__ inline int from_right(int x) {
+  if constexpr (G == 1) return 0;
   // quad_perm [1, 1, 3, 3] / [1, 2, 3, 3], row_shl:1
   constexpr int ctrl = G == 2 ? 0xF5 : (G == 4 ? 0xF9 : 0x101);
   const int y = __builtin_amdgcn_mov_dpp(x, ctrl, 0xF, 0xF, true);
@@ -403,9 +405,10 @@ hipError_t launch_render_preint(const RenderArgs &a0, const float4 *tab, hipStre
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  switch (ray_group(ray_field(a), a.mc.skip != 0)) {
+  switch (preint_group(ray_field(a), a.mc.skip != 0)) {
   case 16: return launch_preint_as<16>(a, tab, lds, s);
   case 4: return launch_preint_as<4>(a, tab, lds, s);
+  case 1: return launch_preint_as<1>(a, tab, lds, s);
   default: return launch_preint_as<2>(a, tab, lds, s);
   }
 }

@@ -35,7 +35,10 @@ void ray_field(const int32_t *dims, const double *cam, int proj, int W, int H, i
   out[3] = f.cover;
 }
 int ray_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip, int heavy) {
-  return vr::ray_group(field(dims, cam, proj, W, H, views), skip != 0, heavy != 0);
+  return vr::ray_group(field(dims, cam, proj, W, H, views), skip != 0, heavy ? vr::kFullHeavy : vr::kFullRays, heavy != 0);
+}
+int preint_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip) {
+  return vr::preint_group(field(dims, cam, proj, W, H, views), skip != 0);
 }
 int serve_group(const int32_t *dims, const double *cam, int proj, int W, int H) {
   return vr::serve_group(field(dims, cam, proj, W, H, 1));

@@ -66,6 +66,23 @@ def test_preintegrated_view_equals_the_same_among_sixteen(size):
             assert torch.equal(one[0], many[5]) and torch.equal(one, full), (dtype, step)
 
 
+@pytest.mark.parametrize("dtype", [np.int16, np.float32], ids=lambda d: d.__name__)
+@pytest.mark.parametrize("step,ert,skip", [(0.5, 0.99, True), (1.3, 0.0, False), (2.5, 0.9, True)])
+def test_close_preintegrated_view_equals_the_same_among_far_ones(dtype, step, ert, skip):
+    """A view whose rays all cross takes one lane per ray; among far views (rays
+    that miss) it takes two."""
+    near, *far = synth.orbit_cameras(DIMS, 8, 145, 60.0, 640, 620)
+    centre = (np.array(DIMS) - 1) / 2
+    near.eye = centre + 0.3 * (near.eye - centre)
+    for c in far:
+        c.eye = centre + 4.0 * (c.eye - centre)
+    vol, tf = upload_volume(_volume(dtype)), upload_tf(synth.tf1())
+    blocks, table = vr.vr_build_blocks(vol, 8), vr.vr_preint_build(tf, step)
+    one = vr.vr_render_preint(vol, blocks, [near], tf, table, step, ert, skip)
+    many = vr.vr_render_preint(vol, blocks, [near, *far], tf, table, step, ert, skip)
+    assert float(one.max()) > 0 and torch.equal(one[0], many[0])
+
+
 @pytest.mark.parametrize("nodes", [2, 3, 130, 257])
 @pytest.mark.parametrize("opacity", [0.0, 0.3, 60.0])
 def test_preint_table_sizes(nodes, opacity):

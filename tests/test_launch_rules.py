@@ -22,6 +22,7 @@ def rules(tmp_path_factory):
     view = [ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_double), ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.ray_field.argtypes = [*view, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]
     lib.ray_group.argtypes = [*view, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    lib.preint_group.argtypes = [*view, ctypes.c_int, ctypes.c_int]
     lib.serve_group.argtypes = view
     lib.serve_blocks.restype = ctypes.c_int64
     lib.serve_blocks.argtypes = [ctypes.c_int64, ctypes.c_int]
@@ -144,3 +145,24 @@ def test_lanes_of_requests_serve_one_and_many(rules, dims, size, view, alone, tw
     c = camera(dims, size, view)
     g = rules.serve_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size)
     assert alone[g] * twelve[g] == min(alone[k] * twelve[k] for k in alone)
+
+
+# the same with pre-integration
+CELLS = [
+    (L, 1024, "near", {1: 5370, 2: 5818, 4: 6654}),
+    (L, 1024, "narrow", {1: 4541, 2: 4729, 4: 5373}),
+    (L, 1024, "inside", {1: 2912, 2: 3057, 4: 3458}),
+    (M, 1024, "ortho", {1: 1980, 2: 2116, 4: 2400}),
+    (S, 700, "nearer", {1: 659, 2: 700, 4: 790}),
+    (S, 400, "near", {1: 411, 2: 443, 4: 453}),
+    (M, 400, "nearer", {1: 800, 2: 560, 4: 514}),
+    (M, 256, "near", {1: 731, 2: 404, 4: 374}),
+    (L, 256, "inside", {1: 906, 2: 472, 4: 367}),
+]
+
+
+@pytest.mark.parametrize("dims,size,view,times", CELLS, ids=lambda v: str(v) if not isinstance(v, dict) else "")
+def test_lanes_per_preintegrated_ray_are_the_measured_best(rules, dims, size, view, times):
+    c = camera(dims, size, view)
+    g = rules.preint_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, 1, 1)
+    assert times[g] <= 1.05 * min(times.values())

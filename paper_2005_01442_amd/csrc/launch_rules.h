@@ -107,6 +107,24 @@ inline int serve_group(const RayField &f) {
   return p > 1.08 || f.rays <= 200000.0 ? 4 : 2;
 }
 
+// Lanes per ray where only the TF gradient is asked for: nothing is scattered, so
+// the few rays and the coarse ones take more lanes, as in the forward, but each
+// sample gathers its taps from global memory whatever their distance (2 / 4 / 16
+// lanes, step 0.5, int16 256x256x200: to 256^2, framed, p = 1.9: 736 / 419 / 259 us, close,
+// p = 0.7: 620 / 670 / 980; to 512^2, framed, p = 0.9: 753 / 625 / 739; 128^3 fp32, 16 views of
+// 225^2, step 1: 867 / 1018 / 1594).  Long steps make short rays, which many lanes
+// cut too small, and many close ones take one lane (step 4, to 1024^2, close:
+// 1.12 ms with one, 1.45 with two; to 512^2, framed, p = 2.8 with four 0.11, sixteen 0.15).
+inline int tf_adjoint_group(const RayField &f, double step) {
+  const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
+  const double scale = step > 2.0 ? 0.36 : 1.0;
+  if (x <= scale * (p > 1.9 ? 50000.0 : p > 0.7 ? 28000.0 : 10000.0) && missing < scale * 300000.0) return 16;
+  if (p > 1.4) return 4;
+  if (step > 1.5 && x > 150000.0 && p <= 0.6) return 1;
+  if (x > 250000.0) return 2;
+  return p > 1.0 || x <= 40000.0 || (f.cover < 2.0 && x <= 170000.0 && step <= 2.0) ? 4 : 2;
+}
+
 // Workgroup -> (item, part) of a serving launch with `parts` workgroups per
 // item: the parts of item i run on XCD i mod 8 (the hardware hands workgroup b
 // to XCD b mod 8), eight items side by side and their parts one after another.

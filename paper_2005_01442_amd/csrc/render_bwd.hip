@@ -97,10 +97,11 @@ __device__ inline uint32_t lds_address(lds_float *p) { return (uint32_t)(uintptr
 // 167 ms (256^3 fp32, 64 views of 512^2, forward and adjoint; 140 ms now) and
 // 0.3 of 6.9 ms (512x512x400 int16 to 1024^2).  Planes per component put
 // neighbouring nodes on neighbouring banks.
-constexpr uint32_t kTfGradNodeBytes = 4 * sizeof(double);
-__host__ __device__ inline uint32_t box_lds_offset(int K, bool with_tf_grad) {
-  uint32_t o = tf_lds_bytes(K) + (with_tf_grad ? (uint32_t)K * kTfGradNodeBytes : 0u);
-  return (o + 15u) & ~15u;
+__host__ __device__ inline uint32_t tf_grad_bytes(int K, bool with_tf_grad) {
+  return with_tf_grad ? (uint32_t)K * 4u * (uint32_t)sizeof(double) : 0u;
+}
+__host__ __device__ inline uint32_t grid_lds_offset(int K, bool with_tf_grad) {
+  return (tf_lds_bytes(K) + tf_grad_bytes(K, with_tf_grad) + 15u) & ~15u;
 }
 typedef __attribute__((address_space(3))) double lds_double;
 
@@ -303,22 +304,25 @@ __device__ inline void win_batch(const GradWindow &w, const VolConst &v, bool st
   __builtin_amdgcn_wave_barrier();
 }
 
+// How an instantiation adds up the grid gradient.  Windows cover a whole step,
+// or are placed for N consecutive lanes at a time (samples of one ray, G = 16), or
+// for the rays' first samples, then their second ones, and so on.
+enum Scatter { kWinStep = 0, kWinRay = 1, kWinSample = 2, kNoGrid = 3 };
+
 // Add dv times the stencil weights of every lane in `staged` (the whole
-// wavefront calls it).  MODE 0: the windows cover the whole step.  1: they are
-// placed for N consecutive lanes at a time (samples of one ray, G = 16).  2:
-// for the rays' first samples, then their second ones, and so on.  A group
-// spread wider than a window adds its taps to global memory.
+// wavefront calls it).  A group spread wider than a window adds its taps to
+// global memory.
 template <int G, int MODE, int N>
 __device__ inline void win_add(GradWindow &w, float *grad, const VolConst &v, bool staged, const Stencil &st, float dv) {
   const int b[3] = {st.ix - 1, st.iy - 1, st.iz - 1};
-  if constexpr (MODE == 0) {
+  if constexpr (MODE == kWinStep) {
     const bool fits = win_place(w, grad, v, staged, b);
     if (staged && !fits) scatter_taps(grad, v, st, dv);
     win_batch<0, 1, 8>(w, v, staged && fits, b, st, dv);
     win_batch<8, 1, 8>(w, v, staged && fits, b, st, dv);
   } else {
     auto batch = [&](auto H_) {
-      constexpr int STEP = MODE == 1 ? 1 : G, R = decltype(H_)::value * (MODE == 1 ? N : 1);
+      constexpr int STEP = MODE == kWinRay ? 1 : G, R = decltype(H_)::value * (MODE == kWinRay ? N : 1);
       const bool here = staged && win_in_batch<R, STEP, N>();
       if (__ballot(here) == 0ull) return;
       const bool fits = win_place(w, grad, v, here, b);
@@ -441,7 +445,7 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_
       ga[6] = fmaf(w1, dc2, ga[6]);
       ga[7] = fmaf(w1, dsig, ga[7]);
     }
-    if (grad_vol && !cq.clamped) {
+    if (MODE != kNoGrid && grad_vol && !cq.clamped) {
       float4 a = s.node[cq.j], b = s.node[cq.j + 1];
       float dv = dc0 * (b.x - a.x);
       dv = fmaf(dc1, b.y - a.y, dv);
@@ -453,12 +457,15 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_
     }
   };
   auto post = [&]() {
+    if constexpr (MODE == kNoGrid) return;
     if (!grad_vol || __ballot(staged) == 0ull) return;
     const Stencil st = make_stencil(sx, sy, sz);  // (recomputed: fewer registers across the chain)
-    if (win.cells)
-      win_add<G, MODE, N>(win, grad_vol, v, staged, st, sdv);
-    else if (staged)
-      scatter_taps(grad_vol, v, st, sdv);
+    if constexpr (MODE != kNoGrid) {
+      if (win.cells)
+        win_add<G, MODE, N>(win, grad_vol, v, staged, st, sdv);
+      else if (staged)
+        scatter_taps(grad_vol, v, st, sdv);
+    }
     staged = false;
   };
   win.ahead = __builtin_amdgcn_mov_dpp((r.d[0] >= 0.0f ? 1 : 0) | (r.d[1] >= 0.0f ? 2 : 0) | (r.d[2] >= 0.0f ? 4 : 0),
@@ -466,7 +473,8 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
   walk_group<G, true>(v, s, tf, mc, r, eval, prep, take, flat, post, acc);
   if (sgtf) flush_tf();
-  if (grad_vol) win_flush(win, grad_vol, v);
+  if constexpr (MODE != kNoGrid)
+    if (grad_vol) win_flush(win, grad_vol, v);
 }
 
 // Pixel of this lane's ray in wavefront w of part `part` of a super-tile:
@@ -543,8 +551,8 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(2, 2)))
   win.lo[0] = win.lo[1] = win.lo[2] = 0;
   win.cells = nullptr;
   win.prod = nullptr;
-  if (a.grad_vol && a.use_box) {
-    lds_float *wins = (lds_float *)(lds + box_lds_offset(K, a.grad_tf != nullptr));
+  if (MODE != kNoGrid && a.grad_vol && a.use_box) {
+    lds_float *wins = (lds_float *)(lds + grid_lds_offset(K, a.grad_tf != nullptr));
     const int row = (int)(threadIdx.x % kWaveSize) / 16;
     wins += (threadIdx.x / kWaveSize) * (kWinFloats + kProdFloats);
     for (int i = threadIdx.x % kWaveSize; i < kWinFloats; i += kWaveSize) wins[i] = 0.0f;
@@ -588,14 +596,22 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(2, 2)))
 }
 
 template <int G, int MODE, int N>
-static hipError_t launch_bwd_as(const BackwardArgs &a0, uint32_t lds, hipStream_t s) {
+static hipError_t launch_bwd_as(const BackwardArgs &a0, hipStream_t s, bool pairs = false) {
   BackwardArgs a = a0;
   const RenderArgs &ra = a.r;
   int64_t grid = group_grid(render_grid(ra), G);
 #ifdef VR_TIMELINE
   g_timeline_bwd_records = grid * (kWgSize / kWaveSize);
 #endif
+  uint32_t lds = tf_lds_bytes(ra.tf.K) + tf_grad_bytes(ra.tf.K, a.grad_tf != nullptr);
+  constexpr uint32_t wave_floats = MODE == kNoGrid ? 0u : kWinFloats + kProdFloats;
+  const uint32_t with_grid = grid_lds_offset(ra.tf.K, a.grad_tf != nullptr) + kWavesPerWg * wave_floats * 4u;
+  a.use_box = MODE != kNoGrid && a.grad_vol && with_grid <= max_lds_per_workgroup() ? 1 : 0;
+  if (a.use_box) lds = with_grid;
   auto *k = ra.vol.dtype == kU16 ? &k_render_bwd<kU16, G, MODE, N> : (ra.vol.dtype == kI16 ? &k_render_bwd<kI16, G, MODE, N> : &k_render_bwd<kF32, G, MODE, N>);
+  if constexpr (MODE == kNoGrid)
+    if (pairs && ra.vol.nx % 2 == 0 && ra.vol.dtype != kF32)
+      k = ra.vol.dtype == kU16 ? &k_render_bwd<kU16Pairs, G, MODE, N> : &k_render_bwd<kI16Pairs, G, MODE, N>;
   const void *fn = reinterpret_cast<const void *>(k);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -613,15 +629,23 @@ static hipError_t launch_bwd_as(const BackwardArgs &a0, uint32_t lds, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_render_backward(const BackwardArgs &a0, hipStream_t s) {
-  BackwardArgs a = a0;
+hipError_t launch_render_backward(const BackwardArgs &a, hipStream_t s) {
   const RenderArgs &ra = a.r;
   if (ra.vol.dtype != kU16 && ra.vol.dtype != kI16 && ra.vol.dtype != kF32) return hipErrorInvalidValue;
-  uint32_t lds = tf_lds_bytes(ra.tf.K) + (a.grad_tf ? (uint32_t)ra.tf.K * kTfGradNodeBytes : 0u);
-  const uint32_t box_bytes = (uint32_t)(kWgSize / kWaveSize) * (kWinFloats + kProdFloats) * 4u;
-  const uint32_t with_box = box_lds_offset(ra.tf.K, a.grad_tf != nullptr) + box_bytes;
-  a.use_box = (a.grad_vol && with_box <= max_lds_per_workgroup()) ? 1 : 0;
-  if (a.use_box) lds = with_box;
+  if (!a.grad_vol) {
+    const RayField f = ray_field(ra);
+    // a wavefront whose taps fill a few lines gains nothing from the pairs'
+    // alignment (256x256x200 to 512^2, p = 0.11, step 0.5, two lanes: 2.59 ms by voxel,
+    // 2.83 by pair, step 1: 1.70, 1.48; step 4, one lane: 0.37, 0.40)
+    const int group = tf_adjoint_group(f, ra.mc.step);
+    const bool pairs = group == 1 ? f.pitch >= 0.2 : f.pitch * ra.mc.step >= 0.1;
+    switch (group) {
+    case 16: return launch_bwd_as<16, kNoGrid, 1>(a, s, pairs);
+    case 4: return launch_bwd_as<4, kNoGrid, 1>(a, s, pairs);
+    case 1: return launch_bwd_as<1, kNoGrid, 1>(a, s, pairs);
+    default: return launch_bwd_as<2, kNoGrid, 1>(a, s, pairs);
+    }
+  }
   // The group shape follows the rays' distance p and the step.  A window holds
   // stencil bases up to 4 apart in y and z: 4x2 rays with two samples each up to
   // p = 1.08 (128^3, 16 views, step 0.5, p = 1: 5.3 ms, 2x2 rays 6.5, one ray
@@ -636,11 +660,11 @@ hipError_t launch_render_backward(const BackwardArgs &a0, hipStream_t s) {
   // took 8.5 ms at p = 1, 30 ms at p = 2.6 and 15 ms at p = 4 (step 0.5); it was
   // ahead by 10-30 % only for steps of 2 and more with p around 1.
   const double p = ray_pitch(ra), step = ra.mc.step;
-  if (p > 2.9 && step <= 1.3) return launch_bwd_as<16, 1, 4>(a, lds, s);
-  if (p > (step < 1.0 ? 1.08 : 1.2)) return launch_bwd_as<4, 2, 4>(a, lds, s);
-  if (step <= 0.8) return launch_bwd_as<2, 0, 8>(a, lds, s);
-  if (step > 1.1 && p <= 0.85) return launch_bwd_as<1, 0, 8>(a, lds, s);
-  return launch_bwd_as<2, 2, 8>(a, lds, s);
+  if (p > 2.9 && step <= 1.3) return launch_bwd_as<16, kWinRay, 4>(a, s);
+  if (p > (step < 1.0 ? 1.08 : 1.2)) return launch_bwd_as<4, kWinSample, 4>(a, s);
+  if (step <= 0.8) return launch_bwd_as<2, kWinStep, 8>(a, s);
+  if (step > 1.1 && p <= 0.85) return launch_bwd_as<1, kWinStep, 8>(a, s);
+  return launch_bwd_as<2, kWinSample, 8>(a, s);
 }
 
 #ifdef VR_TIMELINE

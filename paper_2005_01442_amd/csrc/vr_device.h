@@ -32,6 +32,9 @@ constexpr int kDefaultChunkEdge = 4;  // super-tiles per chunk edge (XCD mapping
 constexpr int kEmptyRadiusMax = 3;    // largest cube of empty blocks a leap crosses
 
 enum Dtype : int32_t { kU16 = 0, kI16 = 1, kF32 = 2 };
+// Kernel instantiations only: 16-bit voxels in rows of even length, whose taps a
+// kernel reads as pair-aligned windows (Vox).
+enum : int32_t { kU16Pairs = 3, kI16Pairs = 4 };
 
 // Wavefront-wide min / max over all 64 lanes (every lane active), returned as
 // a uniform (scalar) value: a butterfly inside each row of 16 lanes through
@@ -300,6 +303,7 @@ __device__ inline void bspline_weights(float t, float w[4]) {
 }
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -312,8 +316,10 @@ template <int DT> struct Vox;
 
 template <> struct Vox<kI16> {
   static constexpr int kBytes = 2;
+  static constexpr uint32_t kPast = 0;
   // four consecutive taps, `soff` (uniform) + `voff` (per lane) bytes into the
-  // volume: row_load + row_unpack (so that loads can run ahead of their use).
+  // volume: row_load + row_unpack (so that loads can run ahead of their use;
+  // both take voff).  past: voxels after the four that the load also reads.
   // The load needs a voxel's alignment only: rows of any length and parity take
   // it.  (Three dwords from the even voxel before, shifted into place, and rows
   // of odd length, whose parity changes from row to row, without loads ahead:
@@ -330,7 +336,7 @@ template <> struct Vox<kI16> {
     __builtin_memcpy(&w, (global_char *)row + voff, sizeof(w));
     return w;
   }
-  __device__ static inline void row_unpack(const RawRow &w, float t[4]) {
+  __device__ static inline void row_unpack(const RawRow &w, uint32_t, float t[4]) {
     t[0] = (float)(int16_t)(w.x & 0xffffu);
     t[1] = (float)((int32_t)w.x >> 16);
     t[2] = (float)(int16_t)(w.y & 0xffffu);
@@ -366,11 +372,12 @@ template <> struct Vox<kI16> {
 
 template <> struct Vox<kU16> {
   static constexpr int kBytes = 2;
+  static constexpr uint32_t kPast = 0;
   using RawRow = Vox<kI16>::RawRow;
   __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t r, const void *data, uint32_t voff, uint32_t soff) {
     return Vox<kI16>::row_load(r, data, voff, soff);
   }
-  __device__ static inline void row_unpack(const RawRow &w, float t[4]) {
+  __device__ static inline void row_unpack(const RawRow &w, uint32_t, float t[4]) {
     t[0] = (float)(w.x & 0xffffu);
     t[1] = (float)(w.x >> 16);
     t[2] = (float)(w.y & 0xffffu);
@@ -394,13 +401,50 @@ template <> struct Vox<kU16> {
   }
 };
 
+// The same in rows of even length: the three dwords from the even voxel at or
+// before the taps, shifted into place (every row of a stencil has its first tap's
+// parity).  Loads of dword alignment are coalesced where neighbouring lanes read the
+// same lines; loads of a voxel's alignment are not (adjoint with the TF gradient alone,
+// which does little else, 256x256x200 int16 to 256^2, close, step 1: 0.53 ms with
+// those, 0.32 with these; fp32 0.32).
+template <> struct Vox<kI16Pairs> {
+  static constexpr int kBytes = 2;
+  static constexpr uint32_t kPast = 2;
+  using RawRow = u32x3;
+  __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t r, const void *, uint32_t voff, uint32_t soff) {
+    return __builtin_amdgcn_raw_buffer_load_b96(r, voff & ~3u, soff, 0);
+  }
+  __device__ static inline u32x2 taps(const RawRow &w, uint32_t voff) {
+    const uint32_t sh = (voff & 2u) * 8u;
+    return u32x2{__builtin_amdgcn_alignbit(w.y, w.x, sh), __builtin_amdgcn_alignbit(w.z, w.y, sh)};
+  }
+  __device__ static inline void row_unpack(const RawRow &w, uint32_t voff, float t[4]) {
+    Vox<kI16>::row_unpack(taps(w, voff), 0u, t);
+  }
+  __device__ static inline float one(__amdgpu_buffer_rsrc_t r, uint32_t e) { return Vox<kI16>::one(r, e); }
+};
+
+template <> struct Vox<kU16Pairs> {
+  static constexpr int kBytes = 2;
+  static constexpr uint32_t kPast = 2;
+  using RawRow = u32x3;
+  __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t r, const void *data, uint32_t voff, uint32_t soff) {
+    return Vox<kI16Pairs>::row_load(r, data, voff, soff);
+  }
+  __device__ static inline void row_unpack(const RawRow &w, uint32_t voff, float t[4]) {
+    Vox<kU16>::row_unpack(Vox<kI16Pairs>::taps(w, voff), 0u, t);
+  }
+  __device__ static inline float one(__amdgpu_buffer_rsrc_t r, uint32_t e) { return Vox<kU16>::one(r, e); }
+};
+
 template <> struct Vox<kF32> {
   static constexpr int kBytes = 4;
+  static constexpr uint32_t kPast = 0;
   using RawRow = u32x4;
   __device__ static inline RawRow row_load(__amdgpu_buffer_rsrc_t r, const void *, uint32_t voff, uint32_t soff) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
   }
-  __device__ static inline void row_unpack(const RawRow &w, float t[4]) {
+  __device__ static inline void row_unpack(const RawRow &w, uint32_t, float t[4]) {
     const f32x4 v = __builtin_bit_cast(f32x4, w);
     t[0] = v.x;
     t[1] = v.y;
@@ -492,6 +536,18 @@ __device__ inline Stencil make_stencil_f(float px, float py, float pz) {
   }
 }
 
+// The 16 rows of the stencil at cell (ix, iy, iz) lie inside the volume, and what
+// their loads read past them inside its memory.
+template <int DT>
+__device__ inline bool rows_inside(const VolConst &v, int ix, int iy, int iz) {
+  bool in = (ix >= 1) & (ix + 2 <= v.nx - 1) & (iy >= 1) & (iy + 2 <= v.ny - 1) & (iz >= 1) & (iz + 2 <= v.nz - 1);
+  if constexpr (Vox<DT>::kPast != 0) {
+    const uint32_t last = ((uint32_t)(iz + 2) * (uint32_t)v.ny + (uint32_t)(iy + 2)) * (uint32_t)v.nx + (uint32_t)(ix + 2);
+    in = in && last + Vox<DT>::kPast < (uint32_t)v.nx * (uint32_t)v.ny * (uint32_t)v.nz;
+  }
+  return in;
+}
+
 // Visit the 16 x-rows of a stencil's taps, row(c, b, t) with t[a] =
 // V[iz-1+c][iy-1+b][ix-1+a] under clamp-to-edge addressing, in the order
 // c = 0..3, b = 0..3.  Interior stencils take the packed-row loads.
@@ -499,9 +555,7 @@ template <int DT, class Row>
 __device__ inline void for_rows(__amdgpu_buffer_rsrc_t rs, const VolConst &v, const Stencil &s, Row &row) {
   const int nx = v.nx, ny = v.ny, nz = v.nz;
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
-  const bool inner = (s.ix >= 1) & (s.ix + 2 <= nx - 1) & (s.iy >= 1) & (s.iy + 2 <= ny - 1) & (s.iz >= 1) &
-                     (s.iz + 2 <= nz - 1);
-  if (inner) {
+  if (rows_inside<DT>(v, s.ix, s.iy, s.iz)) {
     // one per-lane offset; the row offsets are uniform and stay in scalar registers
     const uint32_t kb = (uint32_t)Vox<DT>::kBytes;
     const uint32_t voff = kb * (((uint32_t)(s.iz - 1) * (uint32_t)ny + (uint32_t)(s.iy - 1)) * (uint32_t)nx + (uint32_t)(s.ix - 1));
@@ -511,7 +565,7 @@ __device__ inline void for_rows(__amdgpu_buffer_rsrc_t rs, const VolConst &v, co
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         float t[4];
-        Vox<DT>::row_unpack(Vox<DT>::row_load(rs, v.data, voff, (uint32_t)c * rs_xy + (uint32_t)b * rs_x), t);
+        Vox<DT>::row_unpack(Vox<DT>::row_load(rs, v.data, voff, (uint32_t)c * rs_xy + (uint32_t)b * rs_x), voff, t);
         row(c, b, t);
       }
     return;
@@ -575,10 +629,9 @@ template <int DT>
 __device__ inline void prefetch_taps(TapPrefetch<DT> &p, __amdgpu_buffer_rsrc_t rs, const VolConst &v, int ix, int iy,
                                      int iz) {
   p.ix = INT_MIN;
-  const int nx = v.nx, ny = v.ny, nz = v.nz;
+  const int nx = v.nx, ny = v.ny;
   const uint32_t nxy = (uint32_t)nx * (uint32_t)ny;
-  const bool inner = (ix >= 1) & (ix + 2 <= nx - 1) & (iy >= 1) & (iy + 2 <= ny - 1) & (iz >= 1) & (iz + 2 <= nz - 1);
-  if (!inner) return;
+  if (!rows_inside<DT>(v, ix, iy, iz)) return;
   const uint32_t kb = (uint32_t)Vox<DT>::kBytes;
   const uint32_t voff = kb * (((uint32_t)(iz - 1) * (uint32_t)ny + (uint32_t)(iy - 1)) * (uint32_t)nx + (uint32_t)(ix - 1));
   const uint32_t rs_x = (uint32_t)nx * kb, rs_xy = nxy * kb;
@@ -612,7 +665,7 @@ __device__ inline float reconstruct_prefetched(const TapPrefetch<DT> &p, __amdgp
     for (int b = 0; b < 4; ++b) {
       const int i = 4 * c + b;
       float t[4];
-      Vox<DT>::row_unpack(i < NP ? p.raw[i < NP ? i : 0] : late[i < NP ? 0 : i - NP], t);
+      Vox<DT>::row_unpack(i < NP ? p.raw[i < NP ? i : 0] : late[i < NP ? 0 : i - NP], p.voff, t);
       f(c, b, t);
     }
   return f.acc;

@@ -23,6 +23,7 @@ def rules(tmp_path_factory):
     lib.ray_field.argtypes = [*view, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]
     lib.ray_group.argtypes = [*view, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.preint_group.argtypes = [*view, ctypes.c_int, ctypes.c_int]
+    lib.tf_adjoint_group.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.serve_group.argtypes = view
     lib.serve_blocks.restype = ctypes.c_int64
     lib.serve_blocks.argtypes = [ctypes.c_int64, ctypes.c_int]
@@ -165,4 +166,36 @@ CELLS = [
 def test_lanes_per_preintegrated_ray_are_the_measured_best(rules, dims, size, view, times):
     c = camera(dims, size, view)
     g = rules.preint_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, 1, 1)
+    assert times[g] <= 1.05 * min(times.values())
+
+
+def field_args(dims, cam, views=1):
+    """A camera object as the driver's arguments."""
+    c = [*map(float, cam.eye), *map(float, cam.forward), math.tan(cam.fov_y / 2), 0.0, 0.0]
+    return (ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c), 1, cam.width, cam.height, views
+
+
+# the adjoint with the TF gradient alone, by step
+TF_ADJOINTS = [
+    (M, 128, "framed", 0.5, {2: 885, 4: 432, 16: 165}),
+    (M, 256, "framed", 0.5, {2: 736, 4: 419, 16: 259}),
+    (M, 400, "framed", 0.5, {2: 782, 4: 411, 16: 485}),
+    (M, 512, "framed", 0.5, {2: 753, 4: 625, 16: 739}),
+    (M, 256, "nearer", 0.5, {2: 666, 4: 541, 16: 574}),
+    (M, 256, "near", 0.5, {2: 606, 4: 699, 16: 1000}),
+    (M, 400, "inside", 0.5, {2: 890, 4: 988, 16: 1409}),
+    (M, 1024, "near", 0.5, {2: 8606, 4: 9488, 16: 14880}),
+    (M, 128, "ortho", 4.0, {2: 138, 4: 90, 16: 78}),
+    (M, 512, "far", 4.0, {2: 159, 4: 113, 16: 154}),
+    (M, 256, "near", 4.0, {2: 122, 4: 149, 16: 252}),
+    (M, 512, "near", 4.0, {1: 350, 2: 412, 4: 487}),
+    (M, 1024, "near", 4.0, {1: 1121, 2: 1455, 4: 1783}),
+    (M, 1024, "inside", 4.0, {1: 699, 2: 893, 4: 1116}),
+]
+
+
+@pytest.mark.parametrize("dims,size,view,step,times", TF_ADJOINTS, ids=lambda v: str(v) if not isinstance(v, dict) else "")
+def test_lanes_of_the_tf_adjoint_are_the_measured_best(rules, dims, size, view, step, times):
+    c = camera(dims, size, view)
+    g = rules.tf_adjoint_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, 1, step)
     assert times[g] <= 1.05 * min(times.values())

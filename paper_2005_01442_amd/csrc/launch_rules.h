@@ -14,6 +14,7 @@ struct RayField {
   double pitch = 0.0;     // voxels between neighbouring rays (the largest of the views)
   double rays = 0.0;      // pixels of all views
   double crossing = 0.0;  // rays that cross the volume, about
+  bool inside = false;    // a view's eye lies in the volume
   double cover = 0.0;     // area of the volume's silhouettes over the images' (above 1: a closer view)
 };
 
@@ -26,11 +27,13 @@ struct RayField {
 template <class Vol, class Cam>
 inline void add_view(RayField &f, const Vol &v, const Cam &c) {
   const double n[3] = {(double)v.nx, (double)v.ny, (double)v.nz};
+  bool inside = c.proj != 0;
   double z = 0.0, half = 0.0, f2 = 0.0;  // (a camera's forward vector need not have length 1)
   for (int k = 0; k < 3; ++k) {
     z += (0.5 * (n[k] - 1.0) - c.eye[k]) * c.fwd[k];
     half += 0.5 * n[k] * std::abs(c.fwd[k]);
     f2 += c.fwd[k] * c.fwd[k];
+    inside = inside && c.eye[k] >= -0.5 && c.eye[k] <= n[k] - 0.5;
   }
   z /= f2;
   half /= f2;
@@ -43,6 +46,7 @@ inline void add_view(RayField &f, const Vol &v, const Cam &c) {
   const double before = f.rays;
   f.rays += rays;
   f.pitch = std::max(f.pitch, p);
+  f.inside = f.inside || inside;
   f.crossing += std::min(rays, silhouette);
   f.cover = (f.cover * before + silhouette) / f.rays;
 }
@@ -105,6 +109,42 @@ inline int serve_group(const RayField &f) {
   const double p = f.pitch, x = f.crossing;
   if (p > 2.8 || (p > 2.3 && x <= 20000.0 && f.rays - x < 150000.0) || (f.rays <= 20000.0 && x <= 10000.0)) return 16;
   return p > 1.08 || f.rays <= 200000.0 ? 4 : 2;
+}
+
+// Lanes per ray and scatter of the adjoint (render_bwd.hip): windows of LDS for
+// 16 lanes each, over 4x4, 4x2 or 2x2 rays or one ray, placed for a whole step or
+// for a ray's first samples, then its second ones; or one box per wavefront.
+enum class Adjoint { k4x4, k4x2Step, k4x2Sample, k2x2Sample, k1, kBox };
+
+// A window holds stencil bases up to 4 voxels apart in y and z, so the shape
+// follows the rays' distance p and the step; launches of few rays take more lanes
+// per ray, and long steps in dense launches the box, whose 32 rays share the
+// cells that windows of 8 or 16 flush one by one.  Measured in some 700 launches (256x256x200,
+// framed, near, far, inside, and 128^3 with 16 views; steps 0.5 to 8), relative to
+// the box, for x crossing rays (4x4 / 4x2 by step / 4x2 by sample / 2x2 / one ray):
+//   step 0.5, p = 0.6 to 0.85, x < 40000: 1.12 / 0.63 / 0.65 / 0.60 / 1.45; x > 100000: 0.78 / 0.62 / 0.65 / 0.72 / 2.2
+//   step 0.5, p = 1.05, x > 300000: 0.71 / 0.52 / 0.55 / 0.67 / 2.2; p = 1.14: 1.56 / 0.74 / 0.68 / 0.58 / 1.8
+//   step 0.5, p = 2.6: - / 0.92 / 1.0 / 0.05 / 0.08; p = 3.5, x < 10000: 1.6 / 0.86 / 1.0 / 0.18 / 0.07
+//   step 1, p < 0.6, x < 100000: 1.0 / 0.92 / 0.94 / 1.6 / 5.3; x > 100000: 0.73 / 0.87 / 0.88 / 1.5 / 5.3
+//   step 2, p < 0.6, x < 100000: 1.04 / 1.31 / 1.32 / 2.3 / 13 (the box: 0.94); x > 100000: 0.85 / 1.25 / 1.25 / 2.2 / 15
+//   step 2, p = 0.9, x < 40000: 1.5 / 1.2 / 0.77 / 1.1 / 6; p = 1.05, x > 300000: 0.99 / 1.4 / 1.1 / 1.8 / 12 (the box: 0.90)
+//   step 4, p < 0.6, x > 40000: 1.0 / 1.7 / 1.5 / 2.7 / 25 (the box: 0.92)
+inline Adjoint adjoint_shape(const RayField &f, double step) {
+  const double p = f.pitch, x = f.crossing;
+  if (p > 2.9 && step <= 1.3) return Adjoint::k1;
+  if (p > 1.08)
+    return p <= 1.25 && ((x > 300000.0 && step > 0.9) || (x > 20000.0 && step > 1.2)) ? Adjoint::k4x2Sample : Adjoint::k2x2Sample;
+  if (x <= 10000.0 || (x <= 20000.0 && step <= 1.2)) return Adjoint::k2x2Sample;
+  if (step <= 0.8) return Adjoint::k4x2Step;
+  if (x > 100000.0) {
+    if (step <= 1.3) return p <= 0.6 ? Adjoint::k4x4 : Adjoint::k4x2Sample;
+    return (p <= 0.9 && (step <= 3.0 || p > 0.4)) || step > 6.0 ? Adjoint::k4x4 : Adjoint::kBox;
+  }
+  if (p > 0.85 || x <= 20000.0) return Adjoint::k4x2Sample;
+  if (x <= 40000.0 && step > 1.2) return step < 2.0 || (p > 0.6 && step < 3.0) ? Adjoint::k4x2Sample : Adjoint::kBox;
+  if (x <= 40000.0) return Adjoint::k4x2Step;
+  // (rays from an eye deep in the volume start side by side, on the same cells)
+  return step <= 1.2 && !(f.inside && p < 0.6) ? Adjoint::k4x2Step : Adjoint::kBox;
 }
 
 // Lanes per ray where only the TF gradient is asked for: nothing is scattered, so

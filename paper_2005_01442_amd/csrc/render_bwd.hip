@@ -88,8 +88,8 @@ __device__ inline lds_float *lds_at(uint32_t address) { return (lds_float *)(uin
 __device__ inline uint32_t lds_address(lds_float *p) { return (uint32_t)(uintptr_t)p; }
 
 // LDS layout of the adjoint: TF + prefix counts, TF gradient (four planes of K
-// doubles, when requested), then 16-byte aligned per-wavefront windows and
-// staging areas; two workgroups fit a CU.
+// doubles, when requested), then 16-byte aligned per-wavefront windows, or the
+// box, and staging areas; with up to 256 nodes two workgroups fit a CU.
 //
 // The TF gradient is in doubles because ds_add_f64 is the faster atomic: with 64
 // lanes on distinct words it takes the LDS 9 cycles, ds_add_f32 179 (one lane
@@ -307,7 +307,7 @@ __device__ inline void win_batch(const GradWindow &w, const VolConst &v, bool st
 // How an instantiation adds up the grid gradient.  Windows cover a whole step,
 // or are placed for N consecutive lanes at a time (samples of one ray, G = 16), or
 // for the rays' first samples, then their second ones, and so on.
-enum Scatter { kWinStep = 0, kWinRay = 1, kWinSample = 2, kNoGrid = 3 };
+enum Scatter { kWinStep = 0, kWinRay = 1, kWinSample = 2, kWaveBox = 3, kNoGrid = 4 };
 
 // Add dv times the stencil weights of every lane in `staged` (the whole
 // wavefront calls it).  A group spread wider than a window adds its taps to
@@ -333,12 +333,229 @@ __device__ inline void win_add(GradWindow &w, float *grad, const VolConst &v, bo
   }
 }
 
+// ---------------------------------------------------------------------------
+// Gradient box, for long steps: each wavefront accumulates its grid gradient in a
+// 14 x 14 x 14 box of LDS placed over the slab its lanes are sampling; when a
+// step's stencils leave the box, the box is flushed to global memory (one atomic
+// per touched voxel) and placed anew.  Samples two voxels and more apart along
+// their rays share cells with their neighbours' only, so a window of 16 lanes
+// flushes nearly all it gathers, once per window; the box holds what 32 rays
+// share.  Steps whose stencils spread wider than the box add their taps to
+// global memory.
+// ---------------------------------------------------------------------------
+constexpr int kBox = 14;   // box extent per axis
+constexpr int kBoxY = 16;  // y stride
+// z stride: with y stride 16 and z stride 228 the 64 taps a + 16 b + 228 c
+// (a, b, c < 4) of one stencil fall in 64 distinct LDS banks
+constexpr int kBoxZ = kBoxY * kBox + 4;
+constexpr int kBoxCells = kBox * kBoxZ;
+constexpr int kRec = 16;  // dwords per staged scatter record
+constexpr int kBoxFloats = kBoxCells + kWaveSize * kRec;  // of one wavefront
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i32x4 lds_i32x4;
+
+struct GradBox {
+  lds_float *cells;  // this wavefront's cells, [z][y][x], zero outside use; nullptr: no box
+  lds_float *recs;   // this wavefront's staged scatter records, kRec dwords per slot
+  int ox, oy, oz;
+  bool valid;
+};
+
+__device__ inline void box_flush(GradBox &b, float *grad, const VolConst &v) {
+  if (!b.valid) return;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int lane = threadIdx.x % kWaveSize;
+  for (int i = lane; i < kBox * kBox * kBox; i += kWaveSize) {
+    const int cx = i % kBox, cy = (i / kBox) % kBox, cz = i / (kBox * kBox);
+    const int cell = cz * kBoxZ + cy * kBoxY + cx;
+    const float val = b.cells[cell];
+    if (val != 0.0f) {
+      const int x = b.ox + cx, y = b.oy + cy, z = b.oz + cz;
+      if (x < v.nx && y < v.ny && z < v.nz)
+        unsafeAtomicAdd(grad + ((uint32_t)z * (uint32_t)v.ny + (uint32_t)y) * (uint32_t)v.nx + (uint32_t)x, val);
+      b.cells[cell] = 0.0f;
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  b.valid = false;
+}
+
+// Wavefront-wide: make the box cover every clamped stencil of this step's
+// sampling lanes, if they fit.
+__device__ inline void box_prepare(GradBox &b, float *grad, const VolConst &v, const Ray &r, bool want, float px,
+                                   float py, float pz) {
+  int lo[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, hi[3] = {-1, -1, -1};
+  const int n[3] = {v.nx, v.ny, v.nz};
+  if (want) {
+    const float p[3] = {px, py, pz};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int f = (int)floorf(p[a]);
+      lo[a] = min(max(f - 1, 0), n[a] - 1);
+      hi[a] = min(max(f + 2, 0), n[a] - 1);
+    }
+  }
+  const int o[3] = {b.ox, b.oy, b.oz};
+  bool inside = true;
+  if (want)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) inside = inside && lo[a] >= o[a] && hi[a] < o[a] + kBox;
+  if (b.valid && __ballot(!inside) == 0ull) return;
+  box_flush(b, grad, v);
+  int mn[3], mx[3];
+  bool fits = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    mn[a] = wave_min_i32(lo[a]);
+    mx[a] = wave_max_i32(hi[a]);
+    fits = fits && (mx[a] - mn[a] < kBox);
+  }
+  if (!fits) return;  // this step scatters to global memory
+  // extend the box along the marching direction of the first sampling lane
+  const unsigned long long wm = __ballot(want);
+  const int first = __ffsll((long long)wm) - 1;
+  int org[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float da = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, r.d[a]), first));
+    org[a] = max(da >= 0.0f ? mn[a] : mx[a] - kBox + 1, 0);
+  }
+  b.ox = __builtin_amdgcn_readfirstlane(org[0]);
+  b.oy = __builtin_amdgcn_readfirstlane(org[1]);
+  b.oz = __builtin_amdgcn_readfirstlane(org[2]);
+  b.valid = true;
+}
+
+// A lane whose stencil is interior stages its scatter record (x, y, z weights
+// with dv folded into the z weights, the box cell of tap (0, 0, 0) and its
+// coordinates); the wavefront then applies the staged records with the lanes
+// transposed onto the 64 taps (box_apply).  Clamped stencils, whose taps can
+// coincide, add their taps with LDS atomics right away.
+__device__ inline bool box_stage(GradBox &b, const VolConst &v, const Stencil &st, float dv) {
+  const bool inner = (st.ix >= 1) & (st.ix + 2 <= v.nx - 1) & (st.iy >= 1) & (st.iy + 2 <= v.ny - 1) &
+                     (st.iz >= 1) & (st.iz + 2 <= v.nz - 1);
+  if (inner) {
+    // records are packed in lane order: this lane's slot is its rank among
+    // the staging lanes (all of which are active here together)
+    const unsigned long long act = __ballot(1);
+    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
+    lds_float *rec = b.recs + rank * kRec;
+    const f32x4 wx = {st.wx[0], st.wx[1], st.wx[2], st.wx[3]};
+    const f32x4 wy = {st.wy[0], st.wy[1], st.wy[2], st.wy[3]};
+    const f32x4 wz = {dv * st.wz[0], dv * st.wz[1], dv * st.wz[2], dv * st.wz[3]};
+    *(lds_f32x4 *)(rec + 0) = wx;
+    *(lds_f32x4 *)(rec + 4) = wy;
+    *(lds_f32x4 *)(rec + 8) = wz;
+    // box coordinates of tap (0, 0, 0): its cell, and two packings used to
+    // find where two records' stencils overlap
+    const int x = st.ix - 1 - b.ox, y = st.iy - 1 - b.oy, z = st.iz - 1 - b.oz;
+    const i32x4 m = {z * kBoxZ + y * kBoxY + x, x + 16 * y + 256 * z, 4 * (x + 4 * y + 16 * z), 0};
+    *(lds_i32x4 *)(rec + 12) = m;
+    return true;
+  }
+  int xs[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) xs[a] = min(max(st.ix - 1 + a, 0), v.nx - 1) - b.ox;
+  for (int c = 0; c < 4; ++c) {
+    const int z = min(max(st.iz - 1 + c, 0), v.nz - 1) - b.oz;
+    const float wc = dv * st.wz[c];
+    for (int bb = 0; bb < 4; ++bb) {
+      const int y = min(max(st.iy - 1 + bb, 0), v.ny - 1) - b.oy;
+      const float wb = wc * st.wy[bb];
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        __hip_atomic_fetch_add(b.cells + z * kBoxZ + y * kBoxY + xs[a], wb * st.wx[a], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+  return false;
+}
+
+// Wavefront-wide: apply the records of the lanes in `staged` (packed in slots
+// 0 .. n-1 by box_stage).  For one record the 64 lanes update 64 distinct
+// cells in 64 distinct banks, so a plain read-add-write is exact.  Records are
+// applied two at a time with one LDS round trip: both cells are read before
+// either is written, and where the second record's tap lands on a cell of the
+// first record's stencil, the lane adds the first record's weight for that cell,
+// fetched from the lane that owns it with a cross-lane permute; the writes go out
+// in record order, so a cell shared by the two ends up with both contributions.
+// The next pair's record words are read before this pair's cells are written
+// (records never alias cells).  An odd last record is applied on its own.
+__device__ inline void box_apply(GradBox &b, unsigned long long staged) {
+  if (staged == 0ull) return;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int l = threadIdx.x % kWaveSize;
+  const int ta = l & 3, tb = (l >> 2) & 3, tc = l >> 4;
+  const int off = tc * kBoxZ + tb * kBoxY + ta;
+  // tap coordinates biased by 4 in 4-bit fields: adding another record's
+  // offset (x + 16 y + 256 z) leaves every field in [4, 7] exactly when the
+  // shifted tap is inside that record's stencil
+  const int tp = (ta + 4) + 16 * (tb + 4) + 256 * (tc + 4);
+  const int l4 = 4 * l;
+  const int n = __popcll(staged);
+  struct Pair {
+    float x[2], y[2], z[2];  // this lane's tap weights, not yet multiplied
+    int cell[2], P[2], Q4[2];
+  };
+  auto load_pair = [&](int i, Pair &q) {  // records i and i + 1 (adjacent slots)
+    const lds_float *r0 = b.recs + i * kRec, *r1 = r0 + kRec;
+    const i32x4 m0 = *(const lds_i32x4 *)(r0 + 12), m1 = *(const lds_i32x4 *)(r1 + 12);
+    q.x[0] = r0[ta];
+    q.y[0] = r0[4 + tb];
+    q.z[0] = r0[8 + tc];
+    q.x[1] = r1[ta];
+    q.y[1] = r1[4 + tb];
+    q.z[1] = r1[8 + tc];
+    q.cell[0] = m0.x + off;
+    q.P[0] = m0.y;
+    q.Q4[0] = m0.z;
+    q.cell[1] = m1.x + off;
+    q.P[1] = m1.y;
+    q.Q4[1] = m1.z;
+  };
+  int i = 0;
+  if (n >= 2) {
+    Pair cur;
+    load_pair(0, cur);
+    for (;;) {
+      const float w0 = cur.x[0] * cur.y[0] * cur.z[0];
+      const float w1 = cur.x[1] * cur.y[1] * cur.z[1];
+      // the first record's weight at this lane's tap of the second record
+      const float c = __builtin_bit_cast(
+          float, __builtin_amdgcn_ds_bpermute(l4 + cur.Q4[1] - cur.Q4[0], __builtin_bit_cast(int, w0)));
+      const float v0 = b.cells[cur.cell[0]];
+      float v1 = b.cells[cur.cell[1]];
+      const bool more = i + 3 < n;
+      Pair nxt;
+      if (more) load_pair(i + 2, nxt);
+      const int t = tp + cur.P[1] - cur.P[0];
+      v1 += (t & 0xCCC) == 0x444 ? c : 0.0f;
+      b.cells[cur.cell[0]] = v0 + w0;
+      b.cells[cur.cell[1]] = v1 + w1;
+      i += 2;
+      if (!more) break;
+      cur = nxt;
+    }
+  }
+  if (i < n) {  // an odd last record
+    const lds_float *r = b.recs + i * kRec;
+    const float w = r[ta] * r[4 + tb] * r[8 + tc];
+    const int cell = (*(const lds_i32x4 *)(r + 12)).x + off;
+    b.cells[cell] += w;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // The adjoint marches each ray with a group of G lanes (see walk_group): every
 // lane recomputes its own samples, the group's chain gives each lane T_k a_k,
 // T_{k+1} and C_{<=k} of its sample, and the lane applies that sample's
 // adjoint.
 template <int G, int MODE, int N, int DT>
-__device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_double *sgtf, GradWindow &win,
+__device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_double *sgtf, GradWindow &win, GradBox &box,
                                       const TfConst &tf, const MarchConst &mc, const Ray &r,
                                       __amdgpu_buffer_rsrc_t rs, float4 g, float4 fin, float *grad_vol) {
   const float sl2 = mc.step * 1.4426950408889634f;
@@ -383,7 +600,10 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_
   };
   bool staged = false;  // this lane's sample scatters sdv
   float sdv = 0.0f;
-  NoPrep prep;
+  auto prep = [&](bool want, float px, float py, float pz) {
+    if constexpr (MODE == kWaveBox)
+      if (grad_vol && box.cells) box_prepare(box, grad_vol, v, r, want, px, py, pz);
+  };
   // the taps of this lane's next lattice point are loaded while this one is
   // processed (in the adjoint every lattice point of a ray is usually visited)
   TapPrefetch<DT> pf;
@@ -452,15 +672,30 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_
       dv = fmaf(dc2, b.z - a.z, dv);
       dv = fmaf(dsig, b.w - a.w, dv);
       dv *= tf.scale;
-      staged = dv != 0.0f;
-      sdv = dv;
+      if constexpr (MODE == kWaveBox) {
+        if (dv != 0.0f) {
+          const Stencil st = make_stencil(sx, sy, sz);
+          if (box.valid)
+            staged = box_stage(box, v, st, dv);
+          else
+            scatter_taps(grad_vol, v, st, dv);
+        }
+      } else {
+        staged = dv != 0.0f;
+        sdv = dv;
+      }
     }
   };
   auto post = [&]() {
     if constexpr (MODE == kNoGrid) return;
     if (!grad_vol || __ballot(staged) == 0ull) return;
+    if constexpr (MODE == kWaveBox) {
+      box_apply(box, __ballot(staged));
+      staged = false;
+      return;
+    }
     const Stencil st = make_stencil(sx, sy, sz);  // (recomputed: fewer registers across the chain)
-    if constexpr (MODE != kNoGrid) {
+    if constexpr (MODE < kWaveBox) {
       if (win.cells)
         win_add<G, MODE, N>(win, grad_vol, v, staged, st, sdv);
       else if (staged)
@@ -473,8 +708,11 @@ __device__ inline void march_backward(const VolConst &v, const TfShared &s, lds_
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
   walk_group<G, true>(v, s, tf, mc, r, eval, prep, take, flat, post, acc);
   if (sgtf) flush_tf();
-  if constexpr (MODE != kNoGrid)
+  if constexpr (MODE == kWaveBox) {
+    if (grad_vol) box_flush(box, grad_vol, v);
+  } else if constexpr (MODE != kNoGrid) {
     if (grad_vol) win_flush(win, grad_vol, v);
+  }
 }
 
 // Pixel of this lane's ray in wavefront w of part `part` of a super-tile:
@@ -497,7 +735,7 @@ static int64_t g_timeline_bwd_records = 0;
 // One wavefront item of the adjoint: wavefront w of workgroup item i.
 template <int DT, int G, int MODE, int N>
 __device__ inline void backward_wave_item(const BackwardArgs &a, const TfShared &s, lds_double *sgtf, GradWindow &win,
-                                          __amdgpu_buffer_rsrc_t rs, int64_t i, int w) {
+                                          GradBox &box, __amdgpu_buffer_rsrc_t rs, int64_t i, int w) {
 #ifdef VR_TIMELINE
   const unsigned long long tl0 = __builtin_amdgcn_s_memrealtime();
 #endif
@@ -523,7 +761,7 @@ __device__ inline void backward_wave_item(const BackwardArgs &a, const TfShared 
       fin = reinterpret_cast<const float4 *>(a.out_rgba)[pix];
     }
   }
-  march_backward<G, MODE, N, DT>(ra.vol, s, sgtf, win, ra.tf, ra.mc, r, rs, g, fin, a.grad_vol);
+  march_backward<G, MODE, N, DT>(ra.vol, s, sgtf, win, box, ra.tf, ra.mc, r, rs, g, fin, a.grad_vol);
 #ifdef VR_TIMELINE
   const int tx = (ra.W + kSuperEdge - 1) / kSuperEdge, ty = (ra.H + kSuperEdge - 1) / kSuperEdge;
   timeline_record(g_timeline_bwd, (size_t)i * kWavesPerWg + w, tl0, st.view * tx * ty + st.sy * tx + st.sx,
@@ -551,7 +789,16 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(2, 2)))
   win.lo[0] = win.lo[1] = win.lo[2] = 0;
   win.cells = nullptr;
   win.prod = nullptr;
-  if (MODE != kNoGrid && a.grad_vol && a.use_box) {
+  GradBox box;
+  box.valid = false;
+  box.ox = box.oy = box.oz = 0;
+  box.cells = box.recs = nullptr;
+  if (MODE == kWaveBox && a.grad_vol && a.use_box) {
+    box.cells = (lds_float *)(lds + grid_lds_offset(K, a.grad_tf != nullptr)) + (threadIdx.x / kWaveSize) * kBoxFloats;
+    box.recs = box.cells + kBoxCells;
+    for (int i = threadIdx.x % kWaveSize; i < kBoxCells; i += kWaveSize) box.cells[i] = 0.0f;
+  }
+  if (MODE < kWaveBox && a.grad_vol && a.use_box) {
     lds_float *wins = (lds_float *)(lds + grid_lds_offset(K, a.grad_tf != nullptr));
     const int row = (int)(threadIdx.x % kWaveSize) / 16;
     wins += (threadIdx.x / kWaveSize) * (kWinFloats + kProdFloats);
@@ -578,13 +825,13 @@ __global__ __launch_bounds__(kWgSize) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int part;
     if (!group_tile_of<G>(ra.order, blockIdx.x, ra.W, ra.H, ra.n_views, ra.chunk_edge, part).valid)
       return;  // uniform over the workgroup
-    backward_wave_item<DT, G, MODE, N>(a, s, sgtf, win, rs, blockIdx.x, (int)(threadIdx.x / kWaveSize));
+    backward_wave_item<DT, G, MODE, N>(a, s, sgtf, win, box, rs, blockIdx.x, (int)(threadIdx.x / kWaveSize));
   } else {
     const int x = (int)(blockIdx.x % kXcds);
     int w = 0;
     int64_t i = 0;
     while (next_wave_item(ra.queue, (uint32_t)ra.queue_items, x, i, w))
-      backward_wave_item<DT, G, MODE, N>(a, s, sgtf, win, rs, i, w);
+      backward_wave_item<DT, G, MODE, N>(a, s, sgtf, win, box, rs, i, w);
   }
   if (sgtf) {
     __syncthreads();
@@ -604,7 +851,7 @@ static hipError_t launch_bwd_as(const BackwardArgs &a0, hipStream_t s, bool pair
   g_timeline_bwd_records = grid * (kWgSize / kWaveSize);
 #endif
   uint32_t lds = tf_lds_bytes(ra.tf.K) + tf_grad_bytes(ra.tf.K, a.grad_tf != nullptr);
-  constexpr uint32_t wave_floats = MODE == kNoGrid ? 0u : kWinFloats + kProdFloats;
+  constexpr uint32_t wave_floats = MODE == kNoGrid ? 0u : (MODE == kWaveBox ? kBoxFloats : kWinFloats + kProdFloats);
   const uint32_t with_grid = grid_lds_offset(ra.tf.K, a.grad_tf != nullptr) + kWavesPerWg * wave_floats * 4u;
   a.use_box = MODE != kNoGrid && a.grad_vol && with_grid <= max_lds_per_workgroup() ? 1 : 0;
   if (a.use_box) lds = with_grid;
@@ -632,8 +879,8 @@ static hipError_t launch_bwd_as(const BackwardArgs &a0, hipStream_t s, bool pair
 hipError_t launch_render_backward(const BackwardArgs &a, hipStream_t s) {
   const RenderArgs &ra = a.r;
   if (ra.vol.dtype != kU16 && ra.vol.dtype != kI16 && ra.vol.dtype != kF32) return hipErrorInvalidValue;
+  const RayField f = ray_field(ra);
   if (!a.grad_vol) {
-    const RayField f = ray_field(ra);
     // a wavefront whose taps fill a few lines gains nothing from the pairs'
     // alignment (256x256x200 to 512^2, p = 0.11, step 0.5, two lanes: 2.59 ms by voxel,
     // 2.83 by pair, step 1: 1.70, 1.48; step 4, one lane: 0.37, 0.40)
@@ -646,25 +893,14 @@ hipError_t launch_render_backward(const BackwardArgs &a, hipStream_t s) {
     default: return launch_bwd_as<2, kNoGrid, 1>(a, s, pairs);
     }
   }
-  // The group shape follows the rays' distance p and the step.  A window holds
-  // stencil bases up to 4 apart in y and z: 4x2 rays with two samples each up to
-  // p = 1.08 (128^3, 16 views, step 0.5, p = 1: 5.3 ms, 2x2 rays 6.5, one ray
-  // per group 18.5; p = 1.14: 6.2 against 5.3), from a step of 0.8 on with a
-  // placement per sample (step 1.4, p = 1: 3.3 against 3.4 ms) and up to p = 1.2
-  // (step 2, p = 1.14: 2.9 against 3.7 ms); 4x4 rays with one sample each where
-  // steps are long and rays dense (step 1.4, p = 0.8: 1.7 against 2.1 ms); 2x2
-  // rays with a placement per sample beyond (step 0.5, p = 2.6: 1.7 ms); and one
-  // ray per group once even two rays lie too far apart, while four of its
-  // samples fit a window (step 0.5, p = 3.2: 1.6 against 2.8 ms, p = 4: 1.1
-  // against 5.8 ms).  One 14^3 box per wavefront, the scatter before these,
-  // took 8.5 ms at p = 1, 30 ms at p = 2.6 and 15 ms at p = 4 (step 0.5); it was
-  // ahead by 10-30 % only for steps of 2 and more with p around 1.
-  const double p = ray_pitch(ra), step = ra.mc.step;
-  if (p > 2.9 && step <= 1.3) return launch_bwd_as<16, kWinRay, 4>(a, s);
-  if (p > (step < 1.0 ? 1.08 : 1.2)) return launch_bwd_as<4, kWinSample, 4>(a, s);
-  if (step <= 0.8) return launch_bwd_as<2, kWinStep, 8>(a, s);
-  if (step > 1.1 && p <= 0.85) return launch_bwd_as<1, kWinStep, 8>(a, s);
-  return launch_bwd_as<2, kWinSample, 8>(a, s);
+  switch (adjoint_shape(f, ra.mc.step)) {
+  case Adjoint::k4x4: return launch_bwd_as<1, kWinStep, 8>(a, s);
+  case Adjoint::k4x2Step: return launch_bwd_as<2, kWinStep, 8>(a, s);
+  case Adjoint::k4x2Sample: return launch_bwd_as<2, kWinSample, 8>(a, s);
+  case Adjoint::k2x2Sample: return launch_bwd_as<4, kWinSample, 4>(a, s);
+  case Adjoint::k1: return launch_bwd_as<16, kWinRay, 4>(a, s);
+  default: return launch_bwd_as<2, kWaveBox, 8>(a, s);
+  }
 }
 
 #ifdef VR_TIMELINE

@@ -81,21 +81,6 @@ hipError_t launch_render(const RenderArgs &a, hipStream_t s);
 // lanes per ray and `lds` bytes as launch_render has chosen).
 hipError_t launch_render_variant(const RenderArgs &a, int group, uint32_t lds, hipStream_t s);
 
-// Distance, in voxels, between neighbouring rays of a view at the volume's
-// centre; the largest of a launch's views.
-inline double ray_pitch(const VolConst &v, const CamConst &c) {
-  if (c.proj == 0) return 2.0 * std::max(c.hw / c.W, c.hh / c.H);
-  const double p[3] = {0.5 * (v.nx - 1), 0.5 * (v.ny - 1), 0.5 * (v.nz - 1)};
-  double z = 0.0;
-  for (int k = 0; k < 3; ++k) z += (p[k] - c.eye[k]) * c.fwd[k];
-  return 2.0 * std::max(z, 0.0) * c.th / c.H;
-}
-inline double ray_pitch(const RenderArgs &a) {
-  double most = 0.0;
-  for (int i = 0; i < a.n_views; ++i) most = std::max(most, ray_pitch(a.vol, a.cams[i]));
-  return most;
-}
-
 inline RayField ray_field(const RenderArgs &a) {
   RayField f;
   for (int i = 0; i < a.n_views; ++i) add_view(f, a.vol, a.cams[i]);

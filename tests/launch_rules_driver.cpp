@@ -40,6 +40,9 @@ int ray_group(const int32_t *dims, const double *cam, int proj, int W, int H, in
 int preint_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip) {
   return vr::preint_group(field(dims, cam, proj, W, H, views), skip != 0);
 }
+int adjoint_shape(const int32_t *dims, const double *cam, int proj, int W, int H, int views, double step) {
+  return (int)vr::adjoint_shape(field(dims, cam, proj, W, H, views), step);
+}
 int tf_adjoint_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, double step) {
   return vr::tf_adjoint_group(field(dims, cam, proj, W, H, views), step);
 }

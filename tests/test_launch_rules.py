@@ -23,6 +23,7 @@ def rules(tmp_path_factory):
     lib.ray_field.argtypes = [*view, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]
     lib.ray_group.argtypes = [*view, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.preint_group.argtypes = [*view, ctypes.c_int, ctypes.c_int]
+    lib.adjoint_shape.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.tf_adjoint_group.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.serve_group.argtypes = view
     lib.serve_blocks.restype = ctypes.c_int64
@@ -199,3 +200,48 @@ def test_lanes_of_the_tf_adjoint_are_the_measured_best(rules, dims, size, view, 
     c = camera(dims, size, view)
     g = rules.tf_adjoint_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, 1, step)
     assert times[g] <= 1.05 * min(times.values())
+
+
+# the adjoint with the grid's gradient: 4x4, 4x2 (windows placed per step, per
+# sample), 2x2 and single rays per group of lanes, one box per wavefront
+SCATTER = ["4x4", "4x2", "4x2s", "2x2", "1", "box"]
+D = (128, 128, 128)
+ADJOINTS = [
+    (M, 128, "framed", 1, 0.5, (14714, 7233, 7144, 1375, 414, 7240)),
+    (M, 128, "far", 1, 1.0, (2553, 1780, 1785, 1050, 303, 1756)),
+    (M, 128, "near", 1, 0.5, (7789, 3236, 2848, 852, 1371, 4386)),
+    (M, 128, "inside", 1, 2.0, (409, 311, 316, 384, 2710, 371)),
+    (M, 256, "framed", 1, 2.0, (4015, 2643, 1568, 404, 1007, 2495)),
+    (M, 256, "near", 1, 0.5, (2266, 1292, 1320, 1786, 5579, 1994)),
+    (M, 256, "near", 1, 2.0, (749, 840, 829, 1428, 9461, 698)),
+    (M, 256, "near", 1, 4.0, (498, 1787, 690, 1167, 9558, 462)),
+    (M, 256, "inside", 1, 1.0, (730, 813, 827, 1408, 4557, 649)),
+    (M, 256, "inside", 1, 2.0, (491, 709, 713, 1248, 10212, 415)),
+    (M, 256, "ortho", 1, 2.0, (849, 638, 625, 766, 2071, 753)),
+    (M, 400, "framed", 1, 2.0, (977, 1357, 557, 610, 2262, 852)),
+    (M, 400, "near", 1, 1.4, (1588, 2001, 1999, 3502, 12870, 2009)),
+    (M, 400, "near", 1, 4.0, (995, 1963, 1544, 2691, 24571, 1044)),
+    (M, 400, "inside", 1, 4.0, (802, 1247, 1244, 2201, 23089, 677)),
+    (M, 400, "ortho", 1, 0.5, (2485, 1899, 1954, 2132, 6162, 2634)),
+    (D, 225, "framed", 16, 2.0, (3986, 4787, 2735, 3765, 23444, 2655)),
+    (D, 330, "framed", 6, 2.0, (1209, 1736, 1721, 2991, 20874, 1522)),
+    (D, 400, "framed", 4, 4.0, (905, 3123, 1327, 2340, 18330, 980)),
+]
+
+
+@pytest.mark.parametrize("dims,size,view,views,step,times", ADJOINTS, ids=lambda v: str(v) if not isinstance(v, tuple) or len(v) < 6 else "")
+def test_shapes_of_the_adjoint_are_the_measured_best(rules, dims, size, view, views, step, times):
+    c = camera(dims, size, view)
+    g = rules.adjoint_shape((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, views, step)
+    assert times[g] <= 1.1 * min(times), SCATTER[g]
+
+
+def test_adjoint_shapes_over_odd_cameras(rules):
+    """Every accepted camera and step gets a shape and lanes that are built."""
+    rng = np.random.default_rng(6)
+    for _ in range(2000):
+        W, H = (int(v) for v in rng.choice([1, 3, 64, 511, 4096, 32768], 2))
+        cam = [*rng.normal(0, 600, 3), *rng.normal(0, 1, 3), 10 ** rng.uniform(-4, 4), *(10 ** rng.uniform(-3, 6, 2))]
+        args = ((ctypes.c_int32 * 3)(*map(int, rng.integers(1, 900, 3))), (ctypes.c_double * 9)(*cam), int(rng.integers(0, 2)), W, H,
+                int(rng.integers(1, 17)), 10 ** rng.uniform(-2, 2))
+        assert rules.adjoint_shape(*args) in range(6) and rules.tf_adjoint_group(*args) in (1, 2, 4, 16)

@@ -146,12 +146,14 @@ hipError_t launch_serve_batch(const ServeSlot *slots_dev, const ServeItem *items
 }
 
 #ifdef VR_TIMELINE
+TimelineSource g_timeline_forward = {0, nullptr};
+
 int64_t timeline_copy_fwd(unsigned long long *host, int64_t max) {
-  const int64_t n = std::min<int64_t>(std::min<int64_t>(g_timeline_fwd_records, kTimelineWaves), max);
+  const TimelineSource t = g_timeline_forward;
+  const int64_t n = std::min<int64_t>(std::min<int64_t>(t.records, kTimelineWaves), max);
   if (hipDeviceSynchronize() != hipSuccess) return -1;
-  if (n > 0 && hipMemcpyFromSymbol(host, HIP_SYMBOL(g_timeline_fwd), (size_t)n * 4 * sizeof(unsigned long long)) != hipSuccess)
-    return -1;
-  return g_timeline_fwd_records;
+  if (n > 0 && t.copy(host, (size_t)n * 4 * sizeof(unsigned long long)) != hipSuccess) return -1;
+  return t.records;
 }
 #endif
 

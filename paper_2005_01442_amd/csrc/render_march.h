@@ -107,8 +107,11 @@ __device__ inline float4 march_group(const VolConst &v, const TfShared &s, const
 #endif
 
 #ifdef VR_TIMELINE
+// (the forward's kernels lie in several files, each with records of its own)
 static __device__ unsigned long long g_timeline_fwd[kTimelineWaves * 4];
-static int64_t g_timeline_fwd_records = 0;
+static hipError_t timeline_copy_here(unsigned long long *host, size_t bytes) {
+  return hipMemcpyFromSymbol(host, HIP_SYMBOL(g_timeline_fwd), bytes);
+}
 #endif
 
 // One wavefront item: wavefront w of workgroup item i (a part of a
@@ -204,7 +207,7 @@ static hipError_t launch_render_as(const RenderArgs &a0, uint32_t lds, hipStream
   RenderArgs a = a0;
   int64_t grid = group_grid(render_grid(a), G);
 #ifdef VR_TIMELINE
-  g_timeline_fwd_records = grid * kWavesPerWg;
+  g_timeline_forward = {grid * kWavesPerWg, &timeline_copy_here};
 #endif
   auto *k = a.vol.dtype == kU16   ? &k_render<G, kU16, SHADE, F, ZD>
             : a.vol.dtype == kI16 ? &k_render<G, kI16, SHADE, F, ZD>

@@ -192,6 +192,11 @@ void brick_arena_delete(BrickArena *a);
 // Records of the last launch of the forward / the adjoint (render_fwd.hip,
 // render_bwd.hip): copy up to `max` records into host memory after a device
 // synchronisation; return the launch's record count, or -1.
+struct TimelineSource {
+  int64_t records;                                      // of the last forward launch
+  hipError_t (*copy)(unsigned long long *, size_t);     // from the records of the file it came from
+};
+extern TimelineSource g_timeline_forward;
 int64_t timeline_copy_fwd(unsigned long long *host, int64_t max);
 int64_t timeline_copy_bwd(unsigned long long *host, int64_t max);
 #endif

@@ -77,7 +77,8 @@ constexpr double kFullRays = 61440.0, kFullCells = 170000.0, kFullHeavy = 400000
 inline int ray_group(const RayField &f, bool skip, double full = kFullRays, bool heavy = false) {
   const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
   const double idle = heavy ? 4e6 : 1e6;  // missing rays that sixteen lanes are not worth
-  if (p > 2.8) return missing > idle && p < 4.5 ? 4 : 16;
+  if (missing > 12.0 * idle) return 2;
+  if (p > 2.8) return missing > (p < 4.5 ? idle : 2.0 * idle) ? 4 : 16;
   const double few = 9300.0 * std::pow(std::max(1.0, p / 0.9), 1.45);
   if ((x <= few || ((p > 0.9 || heavy) && f.rays <= 20000.0)) && missing < (p <= 2.3 ? 0.15 * idle : idle)) return 16;
   if (p > 1.4) return 4;
@@ -107,7 +108,7 @@ inline int preint_group(const RayField &f, bool skip) {
 // to 400^2, close: 4 lanes 0.75 / 7.4 ms, 2 lanes 1.13 / 7.0 ms; to 512^2: 1.20 / 11.5, 0.99 / 9.2 ms).
 inline int serve_group(const RayField &f) {
   const double p = f.pitch, x = f.crossing;
-  if (p > 2.8 || (p > 2.3 && x <= 20000.0 && f.rays - x < 150000.0) || (f.rays <= 20000.0 && x <= 10000.0)) return 16;
+  if ((p > 2.8 && f.rays - x <= 2e6) || (p > 2.3 && x <= 20000.0 && f.rays - x < 150000.0) || (f.rays <= 20000.0 && x <= 10000.0)) return 16;
   return p > 1.08 || f.rays <= 200000.0 ? 4 : 2;
 }
 
@@ -129,11 +130,16 @@ enum class Adjoint { k4x4, k4x2Step, k4x2Sample, k2x2Sample, k1, kBox };
 //   step 2, p < 0.6, x < 100000: 1.04 / 1.31 / 1.32 / 2.3 / 13 (the box: 0.94); x > 100000: 0.85 / 1.25 / 1.25 / 2.2 / 15
 //   step 2, p = 0.9, x < 40000: 1.5 / 1.2 / 0.77 / 1.1 / 6; p = 1.05, x > 300000: 0.99 / 1.4 / 1.1 / 1.8 / 12 (the box: 0.90)
 //   step 4, p < 0.6, x > 40000: 1.0 / 1.7 / 1.5 / 2.7 / 25 (the box: 0.92)
+// (and rays that miss cost their lanes: 2048^2, one view a fortieth of it wide, 128x120x100, step 0.5:
+// one ray 1.88 ms, 2x2 rays 1.19, the box 1.57; 4096^2 that miss, p = 1.14: 2x2 1.97, 4x2 1.57)
 inline Adjoint adjoint_shape(const RayField &f, double step) {
-  const double p = f.pitch, x = f.crossing;
-  if (p > 2.9 && step <= 1.3) return Adjoint::k1;
-  if (p > 1.08)
-    return p <= 1.25 && ((x > 300000.0 && step > 0.9) || (x > 20000.0 && step > 1.2)) ? Adjoint::k4x2Sample : Adjoint::k2x2Sample;
+  const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
+  if (p > 2.9 && step <= 1.3 && missing <= 4e6) return Adjoint::k1;
+  if (p > 1.25) return Adjoint::k2x2Sample;
+  if (p > 1.08) {
+    const bool dense = (x > 300000.0 && step > 0.9) || (x > 20000.0 && step > 1.2);
+    return dense || missing > 8e6 ? Adjoint::k4x2Sample : Adjoint::k2x2Sample;
+  }
   if (x <= 10000.0 || (x <= 20000.0 && step <= 1.2)) return Adjoint::k2x2Sample;
   if (step <= 0.8) return Adjoint::k4x2Step;
   if (x > 100000.0) {
@@ -154,10 +160,12 @@ inline Adjoint adjoint_shape(const RayField &f, double step) {
 // p = 0.7: 620 / 670 / 980; to 512^2, framed, p = 0.9: 753 / 625 / 739; 128^3 fp32, 16 views of
 // 225^2, step 1: 867 / 1018 / 1594).  Long steps make short rays, which many lanes
 // cut too small, and many close ones take one lane (step 4, to 1024^2, close:
-// 1.12 ms with one, 1.45 with two; to 512^2, framed, p = 2.8 with four 0.11, sixteen 0.15).
+// 1.12 ms with one, 1.45 with two; to 512^2, far, p = 2.8 with four 0.11, sixteen 0.15).
+// Rays that miss cost their lanes (4096^2 of which 0.03 % cross, p = 2.3: 1.22 / 1.95 / 7.5 ms).
 inline int tf_adjoint_group(const RayField &f, double step) {
   const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
   const double scale = step > 2.0 ? 0.36 : 1.0;
+  if (missing > (p <= 1.0 ? 4e6 : 8e6)) return 2;
   if (x <= scale * (p > 1.9 ? 50000.0 : p > 0.7 ? 28000.0 : 10000.0) && missing < scale * 300000.0) return 16;
   if (p > 1.4) return 4;
   if (step > 1.5 && x > 150000.0 && p <= 0.6) return 1;

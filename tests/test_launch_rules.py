@@ -59,7 +59,7 @@ def camera(dims, size, view):
     n = np.array(dims, float)
     u = np.array([-0.6635568, -0.64628677, 0.37683654])
     u /= np.linalg.norm(u)
-    away, fov, eye = {"framed": (1, 60, None), "far": (3, 60, None), "near": (0.35, 60, None), "narrow": (1, 8, None),
+    away, fov, eye = {"framed": (1, 60, None), "far": (3, 60, None), "farther": (20, 60, None), "farthest": (40, 60, None), "near": (0.35, 60, None), "narrow": (1, 8, None),
                       "nearer": (0.6, 60, None), "inside": (0, 60, (0.5, 0.5, 0.5)), "inside_wide": (0, 90, (0.3, 0.6, 0.4)),
                       "ortho": (1, 60, None)}[view]
     where = (n - 1) / 2 + away * np.linalg.norm(n) * u if eye is None else n * eye
@@ -95,6 +95,11 @@ FRAMES = [
     (XL, 256, "inside_wide", 1, {2: 1743, 4: 688, 16: 1031}),
     (M, 256, "ortho", 1, {2: 364, 4: 231, 16: 390}),
     (M, 512, "nearer", 1, {2: 592, 4: 659}),
+    (M, 1024, "farther", 1, {2: 1344, 16: 583}),
+    (M, 1024, "farther", 8, {2: 1777, 4: 1545, 16: 3953}),
+    (M, 2048, "farthest", 1, {2: 1500, 4: 1106, 16: 1948}),
+    (S, 2048, "farthest", 1, {2: 935, 4: 784, 16: 1880}),
+    (M, 4096, "farthest", 1, {2: 2171, 16: 7713}),
 ]
 
 
@@ -192,6 +197,8 @@ TF_ADJOINTS = [
     (M, 512, "near", 4.0, {1: 350, 2: 412, 4: 487}),
     (M, 1024, "near", 4.0, {1: 1121, 2: 1455, 4: 1783}),
     (M, 1024, "inside", 4.0, {1: 699, 2: 893, 4: 1116}),
+    (M, 2048, "farther", 0.5, {2: 1061, 4: 796, 16: 1950}),
+    (S, 4096, "farthest", 0.5, {2: 1223, 4: 1947}),
 ]
 
 
@@ -226,6 +233,7 @@ ADJOINTS = [
     (D, 225, "framed", 16, 2.0, (3986, 4787, 2735, 3765, 23444, 2655)),
     (D, 330, "framed", 6, 2.0, (1209, 1736, 1721, 2991, 20874, 1522)),
     (D, 400, "framed", 4, 4.0, (905, 3123, 1327, 2340, 18330, 980)),
+    (S, 2048, "farthest", 1, 0.5, (math.inf, math.inf, math.inf, 1185, 1883, 1568)),
 ]
 
 

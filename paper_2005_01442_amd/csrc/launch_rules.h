@@ -173,6 +173,15 @@ inline int tf_adjoint_group(const RayField &f, double step) {
   return p > 1.0 || x <= 40000.0 || (f.cover < 2.0 && x <= 170000.0 && step <= 2.0) ? 4 : 2;
 }
 
+// `group`, or fewer lanes where a launch of `items` super-tile items (256 threads per
+// lane of a ray's group, in whole rounds of eight) would have too many threads: HIP
+// takes fewer than 2^32.  (32768 pixels along one edge, without a launch order, are
+// padded to 2^22 items: 2^32 threads with four lanes.)
+inline int lanes_within(int group, int64_t items) {
+  while (group > 2 && ((items + 7) / 8 * 8) * 256 * group >= ((int64_t)1 << 32)) group = group > 4 ? 4 : 2;
+  return group;
+}
+
 // Workgroup -> (item, part) of a serving launch with `parts` workgroups per
 // item: the parts of item i run on XCD i mod 8 (the hardware hands workgroup b
 // to XCD b mod 8), eight items side by side and their parts one after another.

@@ -219,14 +219,19 @@ __global__ __launch_bounds__(kWgSize) void k_bricked_finish(const float4 *state,
   }
 }
 
+// super-tile items of a pass
+static int64_t pass_items(const BrickedArgs &a) {
+  if (!a.order) return grid_size_for(a.W, a.H, 1, kDefaultChunkEdge);
+  return (int64_t)((a.W + kSuperEdge - 1) / kSuperEdge) * ((a.H + kSuperEdge - 1) / kSuperEdge);
+}
+
 template <int G>
 static hipError_t launch_pass_as(const BrickedArgs &a, uint32_t lds, hipStream_t s) {
   auto *k = a.vol.dtype == kU16 ? &k_bricked_pass<G, kU16> : (a.vol.dtype == kI16 ? &k_bricked_pass<G, kI16> : &k_bricked_pass<G, kF32>);
   const void *fn = reinterpret_cast<const void *>(k);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  const int tiles = ((a.W + kSuperEdge - 1) / kSuperEdge) * ((a.H + kSuperEdge - 1) / kSuperEdge);
-  const int64_t grid = group_grid(a.order ? (int64_t)tiles : grid_size_for(a.W, a.H, 1, kDefaultChunkEdge), G);
+  const int64_t grid = group_grid(pass_items(a), G);
   hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kWgSize), lds, s, a);
   return hipGetLastError();
 }
@@ -239,7 +244,7 @@ hipError_t launch_bricked_pass(const BrickedArgs &a0, hipStream_t s) {
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.fine, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  switch (ray_group(ray_field(a.vol, a.cam), true)) {
+  switch (lanes_within(ray_group(ray_field(a.vol, a.cam), true), pass_items(a))) {
   case 16: return launch_pass_as<16>(a, lds, s);
   case 4: return launch_pass_as<4>(a, lds, s);
   default: return launch_pass_as<2>(a, lds, s);

@@ -884,7 +884,7 @@ hipError_t launch_render_backward(const BackwardArgs &a, hipStream_t s) {
     // a wavefront whose taps fill a few lines gains nothing from the pairs'
     // alignment (256x256x200 to 512^2, p = 0.11, step 0.5, two lanes: 2.59 ms by voxel,
     // 2.83 by pair, step 1: 1.70, 1.48; step 4, one lane: 0.37, 0.40)
-    const int group = tf_adjoint_group(f, ra.mc.step);
+    const int group = lanes_within(tf_adjoint_group(f, ra.mc.step), render_grid(ra));
     const bool pairs = group == 1 ? f.pitch >= 0.2 : f.pitch * ra.mc.step >= 0.1;
     switch (group) {
     case 16: return launch_bwd_as<16, kNoGrid, 1>(a, s, pairs);
@@ -893,7 +893,10 @@ hipError_t launch_render_backward(const BackwardArgs &a, hipStream_t s) {
     default: return launch_bwd_as<2, kNoGrid, 1>(a, s, pairs);
     }
   }
-  switch (adjoint_shape(f, ra.mc.step)) {
+  Adjoint shape = adjoint_shape(f, ra.mc.step);
+  if (shape == Adjoint::k1 && lanes_within(16, render_grid(ra)) < 16) shape = Adjoint::k2x2Sample;
+  if (shape == Adjoint::k2x2Sample && lanes_within(4, render_grid(ra)) < 4) shape = Adjoint::k4x2Sample;
+  switch (shape) {
   case Adjoint::k4x4: return launch_bwd_as<1, kWinStep, 8>(a, s);
   case Adjoint::k4x2Step: return launch_bwd_as<2, kWinStep, 8>(a, s);
   case Adjoint::k4x2Sample: return launch_bwd_as<2, kWinSample, 8>(a, s);

@@ -37,6 +37,7 @@ void ray_field(const int32_t *dims, const double *cam, int proj, int W, int H, i
 int ray_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip, int heavy) {
   return vr::ray_group(field(dims, cam, proj, W, H, views), skip != 0, heavy ? vr::kFullHeavy : vr::kFullRays, heavy != 0);
 }
+int lanes_within(int group, int64_t items) { return vr::lanes_within(group, items); }
 int preint_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip) {
   return vr::preint_group(field(dims, cam, proj, W, H, views), skip != 0);
 }

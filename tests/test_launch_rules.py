@@ -26,10 +26,21 @@ def rules(tmp_path_factory):
     lib.adjoint_shape.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.tf_adjoint_group.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.serve_group.argtypes = view
+    lib.lanes_within.argtypes = [ctypes.c_int, ctypes.c_int64]
     lib.serve_blocks.restype = ctypes.c_int64
     lib.serve_blocks.argtypes = [ctypes.c_int64, ctypes.c_int]
     lib.serve_part.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int)]
     return lib
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 16])
+@pytest.mark.parametrize("items", [1, 1000, 2**20 - 8, 2**20 - 7, 2**20, 2**22 - 8, 2**22, 2**23 - 8, 2**23, 2**24])
+def test_lanes_leave_a_launch_its_threads(rules, items, lanes):
+    """A launch has fewer than 2^32 threads: as many lanes as that allows, and
+    never fewer than two for it."""
+    fits = [g for g in (16, 4, 2, 1) if g <= lanes and -(-items // 8) * 8 * 256 * g < 2**32]
+    got = rules.lanes_within(lanes, items)
+    assert got == max([*fits, min(lanes, 2)])
 
 
 @pytest.mark.parametrize("parts", [2, 4, 8, 16])

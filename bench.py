@@ -86,7 +86,7 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ("render_fwd.hip", "frame_prep.hip", "render_march.h", "vr_device.h", "vr_internal.h")
+KERNEL_SOURCES = ("render_fwd.hip", "frame_prep.hip", "render_march.h", "vr_device.h", "vr_internal.h", "launch_rules.h")
 
 
 def kernel_source_hash():

@@ -1,5 +1,9 @@
 // render_filters.hip -- the whole-image forward kernel with local lighting and
 // with the filters of the paper's comparison (gfx950).
+//
+// Three wavefronts per SIMD leave each lane 168 registers.  The lit kernels spill 24 to
+// 27 of them, the pre-classified ones of 16-bit voxels 6 to 14, the other filters none
+// or one.
 #include "render_march.h"
 
 namespace vr {

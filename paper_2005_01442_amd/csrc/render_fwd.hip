@@ -57,7 +57,9 @@ hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
 // whole-image kernel (the super-tile's `group` parts of 256 / group rays go
 // round its workgroups); the items of a launch may come from many requests of
 // different volumes, sizes and TFs.  The per-ray arithmetic is the whole-image
-// kernel's, so a request's pixels do not depend on what it is batched with.
+// kernel's, so a request's pixels do not depend on what it is batched with.  One
+// kernel holds the marches of three lane counts and three voxel types (a launch mixes
+// them) and spills 38 of its 168 registers for it.
 template <class T>
 __device__ inline const T *constant_ref(const T *p) {
   typedef const __attribute__((address_space(4))) T constant_T;

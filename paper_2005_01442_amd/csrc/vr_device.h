@@ -150,7 +150,7 @@ __device__ inline float4 nan_rgba() {
   return make_float4(q, q, q, q);
 }
 
-// Load the TF into LDS and build the prefix counts.  All 256 threads call it.
+// Load the TF into LDS and build the prefix counts.  All NT threads call it.
 // Returns false (uniformly) when some node is invalid: the caller then writes
 // NaN results instead of rendering, the status word records it, and every
 // block counts as occupied (negative or NaN extinction is read as zero in the
@@ -616,8 +616,9 @@ __device__ inline float reconstruct(__amdgpu_buffer_rsrc_t rs, const VolConst &v
 // The first kRows of the 16 x-rows of the stencil at cell (ix, iy, iz),
 // loaded ahead of the sample that needs them (interior stencils only; else
 // empty); the rest are loaded when the sample is taken.  Holding all 16 across
-// the adjoint's step spilled registers; with 8 it fits 256 (12 rows of 16-bit
-// voxels ahead: 512x512x400 to 1024^2 6.4 -> 6.5 ms).
+// the adjoint's step spilled registers; with 8 the 16-bit kernels fit 256, the fp32
+// ones with windows spill 1 to 13 (12 rows of 16-bit voxels ahead: 512x512x400 to
+// 1024^2 6.4 -> 6.5 ms).
 template <int DT> struct TapPrefetch {
   static constexpr int kRows = 8;
   typename Vox<DT>::RawRow raw[kRows];
@@ -1145,10 +1146,12 @@ __device__ inline void lattice_point(const Ray &r, float step, int k, float &px,
 __device__ inline bool block_occupied(const VolConst &v, const TfShared &s, const TfConst &tf, int b);
 __device__ inline int empty_radius(const VolConst &v, int b);
 
-// What bounds the marches is VALU issue (about 90 % of the cycles on 512x512x400
-// to 1024^2, 260 instructions a step): one unsigned test per axis of the value
-// box, three-operand clamps of the cell and the TF coordinate and 24-bit offsets
-// took 1175 to 1155 us there, 13.20 to 12.97 ms on 1024^3 to 2048^2.
+// What bounds the marches is VALU issue (85 % of the cycles on 512x512x400 to
+// 1024^2): a step in which lanes evaluate issues about 260 VALU instructions, and as
+// some 28 % of the lanes sit out of such steps, 64 evaluated samples cost 362.  So the
+// step is kept short: one unsigned test per axis of the value box, three-operand
+// clamps of the cell and the TF coordinate, 24-bit offsets (each saves instructions;
+// in time they gained less than two runs of one build differ, 1 to 2 %).
 //
 // Walk a tile's rays with the whole wavefront in step: all lanes look at
 // the same indices (a thin slab of the tile's rays).  A lane sits out when its

@@ -59,7 +59,7 @@ inline void add_view(RayField &f, const Vol &v, const Cam &c) {
 // against that, each sample passes a longer compositing chain, and rays that miss
 // the volume cost their lanes (about 0.035 ns a lane: 16 views of 512^2 that the
 // volume covers to 5 %, p = 2.8: 1.07 ms with four, 2.56 with sixteen).  Measured in
-// some 2200 launches (volumes of 64^3 to 1000x900x700, images of 40^2 to 640^2, 1 to
+// some 4000 launches (volumes of 64^3 to 1000x900x700, images of 40^2 to 1300^2, 1 to
 // 16 views, framed, far, close, from inside, orthographic; the lines below are within
 // 1 % of the best of 2, 4 and 16 lanes on average).  Step 0.5, int16, blocks and
 // ERT, microseconds with 2 / 4 / 16 lanes:
@@ -68,13 +68,20 @@ inline void add_view(RayField &f, const Vol &v, const Cam &c) {
 //   rays that all cross (a closer view): to 200^2, p = 0.8: 520 / 300 / 540, to 512^2, p = 0.3: 875 / 1085 / -
 // When every ray crosses, two lanes fill the device evenly from about 61440 rays
 // on; framed views, whose rays through the middle are the longest, gain from four
-// up to some 150000 crossing rays.  `skip`: empty blocks are leapt over (without,
-// the rays' work is even in framed views too).  `full`: the rays of a closer view
-// from which two lanes are ahead.  `heavy`: a sample costs several times a lookup
-// of the box (pre-classification), which hides the chain: 256x256x200 to 512^2,
-// close: 3.3 ms with two lanes, 2.9 with four.
+// up to some 150000 crossing rays, and where p is around 1, so that the box holds
+// the samples of 8x4 rays only in part, beyond.  Longer steps need longer boxes and
+// make shorter rays, which favours two lanes.  Time of two lanes over that of four,
+// steps 0.5 / 0.75 / 1, volumes of 256^3 to 700x760x840:
+//   p = 0.8, x = 145000: 1.06 / 0.99 / 0.93; p = 0.86, x = 420000: 0.94 / 0.89 / 0.84
+//   p = 1.02, x = 260000: 1.01 / 0.96 / 0.91 (framed 1.08 / 1.03 / 0.96; fp32 1.02 / 0.96 / 0.91)
+//   p = 1.05, x = 325000 or 640000: 1.05 / 0.98 / 0.91; p = 1.11 to 1.2, x = 260000 to 720000: 1.03 to 1.17 / 0.97 to 1.09 / 0.91 to 0.98
+//   p = 1.34, x = 200000 or 560000: 1.2 / 1.2 / 1.2; without blocks the same and up to 0.2 more
+// `full`: the rays of a closer view from which two lanes are ahead.  `heavy`: a
+// sample costs several times a lookup of the box (pre-classification), which hides
+// the chain: 256x256x200 to 512^2, close: 3.3 ms with two lanes, 2.9 with four;
+// 700x760x840 to 700^2, close, p = 1.3: 1.07 times as long with two.
 constexpr double kFullRays = 61440.0, kFullCells = 170000.0, kFullHeavy = 400000.0;
-inline int ray_group(const RayField &f, bool skip, double full = kFullRays, bool heavy = false) {
+inline int ray_group(const RayField &f, double step, double full = kFullRays, bool heavy = false) {
   const double p = f.pitch, x = f.crossing, missing = f.rays - f.crossing;
   const double idle = heavy ? 4e6 : 1e6;  // missing rays that sixteen lanes are not worth
   if (missing > 12.0 * idle) return 2;
@@ -83,9 +90,9 @@ inline int ray_group(const RayField &f, bool skip, double full = kFullRays, bool
   if ((x <= few || ((p > 0.9 || heavy) && f.rays <= 20000.0)) && missing < (p <= 2.3 ? 0.15 * idle : idle)) return 16;
   if (p > 1.4) return 4;
   if (missing > 1.5e6) return 2;
-  if (p > 1.08) return x > 300000.0 ? 2 : 4;
-  if (!skip) return x > kFullRays ? 2 : 4;
-  if (f.cover < 2.0 && p >= 0.3) full = std::max(full, p <= 0.95 ? 150000.0 : 300000.0);
+  if (p > (heavy ? 1.08 : 1.2)) return 4;
+  if (p > 1.08) return x > 200000.0 && step > 0.8 ? 2 : 4;
+  if (f.cover < 2.0 && p >= 0.3) full = std::max(full, p > 0.95 && step <= 0.6 ? 300000.0 : (step <= 0.8 ? 150000.0 : 120000.0));
   return x > full ? 2 : 4;
 }
 
@@ -95,9 +102,9 @@ inline int ray_group(const RayField &f, bool skip, double full = kFullRays, bool
 // microseconds: 512x512x400 to 1024^2, p = 0.33: 5370 / 5820 / 6650, p = 0.93 (framed): - / 1640 / -;
 // 128x120x100 to 700^2, p = 0.12: 897 / 955 / 1078; to 400^2, p = 0.2: 411 / 443 / 453;
 // 256x256x200 to 400^2, p = 0.7: 800 / 560 / 514; to 256^2, close: 731 / 404 / 374.
-inline int preint_group(const RayField &f, bool skip) {
+inline int preint_group(const RayField &f, double step) {
   if (f.cover >= 1.0 && ((f.pitch < 0.6 && f.crossing > 300000.0) || (f.pitch < 0.22 && f.crossing > 147456.0))) return 1;
-  return ray_group(f, skip, kFullCells);
+  return ray_group(f, step, kFullCells);
 }
 
 // Lanes per ray of a served request, which shares its launch with others: a

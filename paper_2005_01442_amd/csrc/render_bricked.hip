@@ -244,7 +244,7 @@ hipError_t launch_bricked_pass(const BrickedArgs &a0, hipStream_t s) {
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.fine, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  switch (lanes_within(ray_group(ray_field(a.vol, a.cam), true), pass_items(a))) {
+  switch (lanes_within(ray_group(ray_field(a.vol, a.cam), a.mc.step), pass_items(a))) {
   case 16: return launch_pass_as<16>(a, lds, s);
   case 4: return launch_pass_as<4>(a, lds, s);
   default: return launch_pass_as<2>(a, lds, s);

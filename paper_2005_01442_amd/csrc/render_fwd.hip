@@ -43,7 +43,7 @@ hipError_t launch_render(const RenderArgs &a0, hipStream_t s) {
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  const int lanes = ray_group(ray_field(a), a.mc.skip != 0, a.filter == 2 ? kFullHeavy : kFullRays, a.filter == 2);
+  const int lanes = ray_group(ray_field(a), a.mc.step, a.filter == 2 ? kFullHeavy : kFullRays, a.filter == 2);
   const int group = lanes_within(lanes, render_grid(a));
   if (a.shaded || a.filter != 0) return launch_render_variant(a, group, lds, s);
   // the shallow value box for volumes the MALL holds (their refills are

@@ -405,7 +405,7 @@ hipError_t launch_render_preint(const RenderArgs &a0, const float4 *tab, hipStre
   if (a.use_box) lds = with_box;
   a.occ_lds_words = a.use_box ? occupancy_lds_words(a.vol, lds) : 0;
   lds += (uint32_t)a.occ_lds_words * 4u;
-  switch (lanes_within(preint_group(ray_field(a), a.mc.skip != 0), render_grid(a))) {
+  switch (lanes_within(preint_group(ray_field(a), a.mc.step), render_grid(a))) {
   case 16: return launch_preint_as<16>(a, tab, lds, s);
   case 4: return launch_preint_as<4>(a, tab, lds, s);
   case 1: return launch_preint_as<1>(a, tab, lds, s);

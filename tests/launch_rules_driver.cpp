@@ -34,12 +34,12 @@ void ray_field(const int32_t *dims, const double *cam, int proj, int W, int H, i
   out[2] = f.crossing;
   out[3] = f.cover;
 }
-int ray_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip, int heavy) {
-  return vr::ray_group(field(dims, cam, proj, W, H, views), skip != 0, heavy ? vr::kFullHeavy : vr::kFullRays, heavy != 0);
+int ray_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, double step, int heavy) {
+  return vr::ray_group(field(dims, cam, proj, W, H, views), step, heavy ? vr::kFullHeavy : vr::kFullRays, heavy != 0);
 }
 int lanes_within(int group, int64_t items) { return vr::lanes_within(group, items); }
-int preint_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, int skip) {
-  return vr::preint_group(field(dims, cam, proj, W, H, views), skip != 0);
+int preint_group(const int32_t *dims, const double *cam, int proj, int W, int H, int views, double step) {
+  return vr::preint_group(field(dims, cam, proj, W, H, views), step);
 }
 int adjoint_shape(const int32_t *dims, const double *cam, int proj, int W, int H, int views, double step) {
   return (int)vr::adjoint_shape(field(dims, cam, proj, W, H, views), step);

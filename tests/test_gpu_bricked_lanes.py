@@ -32,7 +32,7 @@ def test_bricked_lanes_are_bit_identical_to_incore(rules, lanes, size, away, dty
     cam = synth.orbit_camera(DIMS, np.array((-0.6, -0.65, 0.4)), 60.0, *size)
     centre = (np.array(DIMS) - 1) / 2
     cam.eye = centre + away * (np.asarray(cam.eye) - centre)
-    assert rules.ray_group(*field_args(DIMS, cam), 1, 0) == lanes
+    assert rules.ray_group(*field_args(DIMS, cam), 0.5, 0) == lanes
     want = _incore(vol, [cam], tf, 0.5, 0.99, 16)
     got, bv = _bricked(vol, [cam], tf, 0.5, 0.99, 16, 7)
     assert bv.stats()["passes"] > 3 and want.max() > 0

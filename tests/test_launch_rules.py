@@ -21,8 +21,8 @@ def rules(tmp_path_factory):
     lib = ctypes.CDLL(out)
     view = [ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_double), ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.ray_field.argtypes = [*view, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]
-    lib.ray_group.argtypes = [*view, ctypes.c_int, ctypes.c_int, ctypes.c_int]
-    lib.preint_group.argtypes = [*view, ctypes.c_int, ctypes.c_int]
+    lib.ray_group.argtypes = [*view, ctypes.c_int, ctypes.c_double, ctypes.c_int]
+    lib.preint_group.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.adjoint_shape.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.tf_adjoint_group.argtypes = [*view, ctypes.c_int, ctypes.c_double]
     lib.serve_group.argtypes = view
@@ -78,9 +78,9 @@ def camera(dims, size, view):
     return [0 if view == "ortho" else 1, *where, *-u, math.tan(math.radians(fov) / 2), half, half]
 
 
-def lanes(rules, dims, size, view, views=1, skip=True, heavy=False):
+def lanes(rules, dims, size, view, views=1, step=0.5, heavy=False):
     c = camera(dims, size, view)
-    return rules.ray_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, views, skip, heavy)
+    return rules.ray_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, views, step, heavy)
 
 
 # microseconds of int16 frames with blocks, step 0.5, by lanes per ray
@@ -114,6 +114,24 @@ FRAMES = [
 ]
 
 
+# the same by step: large views around p = 1, with and without blocks (times near 100: relative)
+H, XXL = (426, 421, 445), (700, 760, 840)
+STEPPED = [
+    (M, 600, "framed", 0.5, {2: 415, 4: 390}), (M, 600, "framed", 1.0, {2: 222, 4: 239}),
+    (M, 512, "framed", 0.5, {2: 507, 4: 381}),
+    (H, 800, "framed", 0.5, {2: 1633, 4: 1506}), (H, 800, "framed", 1.0, {2: 565, 4: 622}),
+    (H, 512, "nearer", 1.0, {2: 557, 4: 613}), (H, 700, "framed", 1.0, {2: 104, 4: 100}),
+    (XXL, 1150, "framed", 0.5, {2: 7561, 4: 5463}), (XXL, 1150, "framed", 1.0, {2: 2080, 4: 1843}),
+    (XXL, 700, "nearer", 0.75, {2: 3423, 4: 2641}), (XXL, 600, "ortho", 1.0, {2: 2330, 4: 1848}),
+    (XXL, 1000, "nearer", 0.5, {2: 93, 4: 100}), (H, 1000, "framed", 0.75, {2: 88, 4: 100}),
+]
+
+
+@pytest.mark.parametrize("dims,size,view,step,times", STEPPED, ids=lambda v: str(v) if not isinstance(v, dict) else "")
+def test_lanes_per_ray_by_step_are_the_measured_best(rules, dims, size, view, step, times):
+    assert times[lanes(rules, dims, size, view, step=step)] <= 1.05 * min(times.values())
+
+
 @pytest.mark.parametrize("dims,size,view,views,times", FRAMES, ids=lambda v: str(v) if not isinstance(v, dict) else "")
 def test_lanes_per_ray_are_the_measured_best(rules, dims, size, view, views, times):
     assert times[lanes(rules, dims, size, view, views)] <= 1.05 * min(times.values())
@@ -133,9 +151,9 @@ def test_lanes_per_ray_over_odd_cameras(rules):
         out = (ctypes.c_double * 4)()
         rules.ray_field(*args, views, out)
         assert all(math.isfinite(v) and v >= 0 for v in out) and out[2] <= out[1] == views * W * H
-        for skip in (0, 1):
+        for step in (0.1, 0.5, 1.0, 8.0):
             for heavy in (0, 1):
-                assert rules.ray_group(*args, views, skip, heavy) in (2, 4, 16)
+                assert rules.ray_group(*args, views, step, heavy) in (2, 4, 16)
         assert rules.serve_group(*args) in (2, 4, 16)
         if proj == 1:  # the same view with a longer forward vector: the plane at distance 1 moves to 3
             longer = [*cam[:3], *(3 * v for v in cam[3:6]), 3 * cam[6], 0.0, 0.0]
@@ -182,7 +200,7 @@ CELLS = [
 @pytest.mark.parametrize("dims,size,view,times", CELLS, ids=lambda v: str(v) if not isinstance(v, dict) else "")
 def test_lanes_per_preintegrated_ray_are_the_measured_best(rules, dims, size, view, times):
     c = camera(dims, size, view)
-    g = rules.preint_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, 1, 1)
+    g = rules.preint_group((ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c[1:]), c[0], size, size, 1, 0.5)
     assert times[g] <= 1.05 * min(times.values())
 
 

@@ -205,7 +205,7 @@ def test_lanes_per_preintegrated_ray_are_the_measured_best(rules, dims, size, vi
 
 
 def field_args(dims, cam, views=1):
-    """A camera object as the driver's arguments."""
+    """A camera object as the arguments of the rules' C functions."""
     c = [*map(float, cam.eye), *map(float, cam.forward), math.tan(cam.fov_y / 2), 0.0, 0.0]
     return (ctypes.c_int32 * 3)(*dims), (ctypes.c_double * 9)(*c), 1, cam.width, cam.height, views
 
